@@ -116,6 +116,29 @@ __device__ __forceinline__ void sh_basis(float x, float y, float z, float (&Y)[(
     }
 }
 
+// sum_k c_k Y_k of one channel (coefficients from a row: at(i), i = k or more).
+// FP32 degree 3 is summed in four parts of four, the order in which a quad of
+// lanes adds it up (FwdWave), so that every kernel forms the same colours.
+template <int DT, int DEG, class At>
+__device__ __forceinline__ float sh_dot(At at, const float (&Y)[(DEG + 1) * (DEG + 1)]) {
+    constexpr int K = (DEG + 1) * (DEG + 1);
+    if constexpr (DT == DOT_F32 && DEG == 3) {
+        float p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            p[q] = at(4 * q) * Y[4 * q];
+#pragma unroll
+            for (int j = 1; j < 4; ++j) p[q] = fmaf(at(4 * q + j), Y[4 * q + j], p[q]);
+        }
+        return (p[0] + p[1]) + (p[2] + p[3]);
+    } else {
+        float x = 0.f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x = fmaf(at(k), Y[k], x);
+        return x;
+    }
+}
+
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float sigmoidf_(float x) { return fast_rcp(1.f + __expf(-x)); }
 
@@ -210,6 +233,22 @@ __device__ __forceinline__ Ray ray_of(const RayBatch& rb, int64_t rid) {
     r.dz = (double)rb.dirs[3 * rid + 2];
     normalise(r);
     return r;
+}
+
+// The output index of the ray that make_ray gives this lane; false if it has none.
+__device__ __forceinline__ bool ray_index(const RayBatch& rb, int64_t tile, int lane, int64_t& rid) {
+    if (rb.kind == DOT_RAYS_CAMERAS) {
+        int tw = (rb.width + 7) >> 3, th = (rb.height + 7) >> 3;
+        int64_t per = (int64_t)tw * th;
+        int cam = (int)(tile / per);
+        int t = (int)(tile - (int64_t)cam * per);
+        int ty = t / tw, tx = t - ty * tw;
+        int u = tx * 8 + (lane & 7), v = ty * 8 + (lane >> 3);
+        rid = ((int64_t)cam * rb.height + v) * rb.width + u;
+        return u < rb.width && v < rb.height;
+    }
+    rid = tile * WAVE + lane;
+    return rid < rb.n_rays;
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap so that each
@@ -397,6 +436,8 @@ struct FwdSeg {
 
     __device__ FwdSeg(const TreeView& tv_, const FwdArgs& a_) : tv(tv_), a(a_) {}
 
+    __device__ __forceinline__ void begin(const Ray& r) { sh_basis<DEG>((float)r.dx, (float)r.dy, (float)r.dz, Y); }
+
     __device__ __forceinline__ void flush_slot() {
         if constexpr (COUNT)
             if (pend_j >= 0) a.rec.slot[pend_j] = pend_slot;
@@ -456,19 +497,15 @@ struct FwdSeg {
             float cv[3];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                float x = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    float cf;
+                const float x = sh_dot<DT, DEG>([&](int k) {
                     if constexpr (DT == DOT_BF16) {
-                        int i = ch * K + k;
-                        uint32_t wv = packed[i >> 1];
-                        cf = __uint_as_float((i & 1) ? (wv & 0xffff0000u) : (wv << 16));
+                        const int i = ch * K + k;
+                        const uint32_t wv = packed[i >> 1];
+                        return __uint_as_float((i & 1) ? (wv & 0xffff0000u) : (wv << 16));
                     } else {
-                        cf = row[ch * K + k];
+                        return row[ch * K + k];
                     }
-                    x = fmaf(cf, Y[k], x);
-                }
+                }, Y);
                 cv[ch] = sigmoidf_(x);
                 C[ch] = fmaf(w, cv[ch], C[ch]);
             }

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 
 #include <cmath>
@@ -41,6 +42,10 @@ constexpr int LINK_ID_BITS = 27;
 constexpr uint32_t LINK_ID_MASK = (1u << LINK_ID_BITS) - 1u;
 constexpr int64_t LINK_MAX_LEAVES = (int64_t)LINK_ID_MASK;
 
+// Planes of at most this many bytes are read with 32-bit offsets (the rest of
+// the range is left for an offset that means "nothing").
+constexpr uint64_t NEAR_BYTES = 0xffffe000ull;
+
 // Everything a kernel needs to read a tree (passed by value).
 struct TreeView {
     const int32_t* child;
@@ -54,6 +59,7 @@ struct TreeView {
     int sh_stride;    // elements per SH row (of the palette for DOT_PAL16)
     const void* palette;   // DOT_PAL16: FP16 palette rows; `sh` holds uint16 indices
     const uint32_t* links; // face-neighbour links [n_leaves][6], or null (ancestor-stack walk)
+    bool near;             // every plane is within reach of 32-bit byte offsets
 };
 
 struct Alloc {
@@ -126,6 +132,8 @@ struct dot_tree {
         v.sh_stride = sh_stride;
         v.palette = palette;
         v.links = links;
+        const uint64_t L = (uint64_t)n_leaves, row = storage == DOT_PAL16 ? 2 : (uint64_t)sh_stride * dot::storage_bytes(storage);
+        v.near = std::max(L * std::max<uint64_t>(row, 24), (uint64_t)n_internal * 32) <= dot::NEAR_BYTES;
         return v;
     }
 };

@@ -2,29 +2,41 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
-#include "dot_device.h"
+#include "fwd_walk.h"
 
 namespace dot {
 
 // MODE 0: plain; 1: with the traversal counters of dot_render_stats; 2: with
-// the per-leaf segment counts of a training forward
-template <int DT, int DEG, int MODE>
-__global__ __launch_bounds__(BLOCK) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
+// the per-leaf segment counts of a training forward.  FAR: a tree with a plane
+// past the reach of 32-bit offsets, walked lane by lane with 64-bit addresses.
+template <int DT, int DEG, int MODE, bool FAR>
+__global__ __launch_bounds__(BLOCK, FAR ? 1 : fwd_waves(DT, DEG)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
     __shared__ int stack_lds[LAT * BLOCK];
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int64_t nb = gridDim.x;
-    const int64_t tile = xcd_block(blockIdx.x, nb) * WAVES_PER_BLOCK + (tid >> 6);
+    const int64_t tile = xcd_block(blockIdx.x, nb) * WAVES_PER_BLOCK + __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tile >= rb.n_tiles) return;
-    Ray r;
-    int64_t rid;
-    if (!make_ray(rb, tile, lane, r, rid)) return;
-    FwdSeg<DT, DEG, MODE == 2> seg(tv, a);
+    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
+    int64_t rid = 0;
+    const bool live = make_ray(rb, tile, lane, r, rid);
+    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2>> seg(tv, a);
     seg.rid = rid;
-    sh_basis<DEG>((float)r.dx, (float)r.dy, (float)r.dz, seg.Y);
     int desc = 0;
-    traverse(tv, r, &stack_lds[tid], seg, desc);
+    seg.begin(r);
+    if constexpr (FAR) {
+        if (!live) return;
+        traverse(tv, r, &stack_lds[tid], seg, desc);
+    } else {
+        if (tv.links)
+            walk_fwd<true>(tv, r, live, &stack_lds[tid], seg, desc);
+        else
+            walk_fwd<false>(tv, r, live, &stack_lds[tid], seg, desc);
+        // the index again, rather than two registers held through the walk
+        if (!ray_index(rb, tile, lane, rid)) return;
+    }
     if constexpr (MODE == 2) {
         if (a.rec.a) {
             seg.flush_slot();
@@ -79,9 +91,7 @@ struct BwdSeg {
             float c[3];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                float x = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) x = fmaf(row[ch * K + k], Y[k], x);
+                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
                 c[ch] = sigmoidf_(x);
             }
             float gs = 0.f;
@@ -201,9 +211,7 @@ struct BwdSegWave {
             float c[3];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                float x = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) x = fmaf(row[ch * K + k], Y[k], x);
+                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
                 c[ch] = sigmoidf_(x);
             }
             float gs = 0.f;
@@ -340,9 +348,7 @@ struct BwdEmit {
             load_sh_row<DT, 3 * K>(tv.sh, leaf, row);
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                float x = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) x = fmaf(row[ch * K + k], Y[k], x);
+                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
                 P[ch] = fmaf(w, sigmoidf_(x), P[ch]);
             }
             S = Sn;
@@ -357,9 +363,7 @@ struct BwdEmit {
             float c[3];
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                float x = 0.f;
-#pragma unroll
-                for (int k = 0; k < K; ++k) x = fmaf(row[ch * K + k], Y[k], x);
+                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
                 c[ch] = sigmoidf_(x);
             }
             float out[RS];
@@ -1058,31 +1062,33 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s, uint32_t* word
     return hipGetLastError();
 }
 
-template <int DT, int DEG>
-static hipError_t fwd_dispatch_stats(const TreeView& tv, const RayBatch& rb, const FwdArgs& a,
-                                     dim3 grid, hipStream_t s) {
+template <int DT, int DEG, bool FAR>
+static hipError_t fwd_dispatch_mode(const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid, hipStream_t s) {
     if (a.stats)
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 1>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    else if constexpr (DT == DOT_F32) {
-        if (a.leaf_count)
-            hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 2>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-        else
-            hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    } else {
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    }
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 1, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else if (DT == DOT_F32 && a.leaf_count)
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, DT == DOT_F32 ? 2 : 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
     return hipGetLastError();
 }
 
-template <int DT>
+template <int DT, bool FAR>
 static hipError_t fwd_dispatch_deg(int deg, const TreeView& tv, const RayBatch& rb, const FwdArgs& a,
                                    dim3 grid, hipStream_t s) {
     switch (deg) {
-        case 0: return fwd_dispatch_stats<DT, 0>(tv, rb, a, grid, s);
-        case 1: return fwd_dispatch_stats<DT, 1>(tv, rb, a, grid, s);
-        case 2: return fwd_dispatch_stats<DT, 2>(tv, rb, a, grid, s);
-        default: return fwd_dispatch_stats<DT, 3>(tv, rb, a, grid, s);
+        case 0: return fwd_dispatch_mode<DT, 0, FAR>(tv, rb, a, grid, s);
+        case 1: return fwd_dispatch_mode<DT, 1, FAR>(tv, rb, a, grid, s);
+        case 2: return fwd_dispatch_mode<DT, 2, FAR>(tv, rb, a, grid, s);
+        default: return fwd_dispatch_mode<DT, 3, FAR>(tv, rb, a, grid, s);
     }
+}
+
+template <int DT>
+static hipError_t fwd_dispatch_reach(int deg, const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid,
+                                     hipStream_t s) {
+    if (!tv.near) return fwd_dispatch_deg<DT, true>(deg, tv, rb, a, grid, s);
+    return fwd_dispatch_deg<DT, false>(deg, tv, rb, a, grid, s);
 }
 
 hipError_t launch_render_fwd(const dot_tree& t, const RayBatch& rb, const FwdArgs& a, hipStream_t s) {
@@ -1090,10 +1096,10 @@ hipError_t launch_render_fwd(const dot_tree& t, const RayBatch& rb, const FwdArg
     dim3 grid((unsigned)((rb.n_tiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK));
     TreeView tv = t.view();
     switch (t.storage) {
-        case DOT_F32: return fwd_dispatch_deg<DOT_F32>(t.degree, tv, rb, a, grid, s);
-        case DOT_F16: return fwd_dispatch_deg<DOT_F16>(t.degree, tv, rb, a, grid, s);
-        case DOT_PAL16: return fwd_dispatch_deg<DOT_PAL16>(t.degree, tv, rb, a, grid, s);
-        default: return fwd_dispatch_deg<DOT_BF16>(t.degree, tv, rb, a, grid, s);
+        case DOT_F32: return fwd_dispatch_reach<DOT_F32>(t.degree, tv, rb, a, grid, s);
+        case DOT_F16: return fwd_dispatch_reach<DOT_F16>(t.degree, tv, rb, a, grid, s);
+        case DOT_PAL16: return fwd_dispatch_reach<DOT_PAL16>(t.degree, tv, rb, a, grid, s);
+        default: return fwd_dispatch_reach<DOT_BF16>(t.degree, tv, rb, a, grid, s);
     }
 }
 

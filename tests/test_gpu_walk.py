@@ -1,0 +1,77 @@
+"""The forward walk's edges on the GPU: lanes without a ray beside lanes with one, rays along the axes and in cell
+planes, trees past the reach of 32-bit plane offsets, against the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2307_15333_amd import core, synth
+
+from .test_gpu_render import TOL32, oracle_tree, rgb_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("links", [True, False])
+@pytest.mark.parametrize("storage,degree", [("f32", 3), ("f32", 2), ("f32", 0), ("f16", 3), ("bf16", 1)])
+def test_partial_quads_and_waves(storage, degree, links):
+    """Ray counts that leave lanes of a quad or waves of a workgroup empty; half of the rays miss the cube."""
+    s = synth.random_tree_scene(5, degree, seed=31 + degree, p_split=0.5)
+    tree = core.Octree.from_scene(s, storage)
+    tree.set_links(links)
+    ref_tree = oracle_tree(s, storage)
+    for n in (1, 2, 3, 5, 63, 65, 130):
+        o, d = synth.random_explicit_rays(n, seed=n)
+        d[1::2] *= -1.0
+        rgb, ns = tree.render(core.Rays.explicit(o, d), nseg=True)
+        ref = O.render(ref_tree, o, d)
+        assert rgb_err(rgb.cpu().numpy(), ref).max() <= TOL32
+        assert (ns.cpu().numpy()[1::2] == 0).all()
+
+
+@pytest.mark.parametrize("links", [True, False])
+def test_axis_rays_and_cell_planes(links):
+    """Directions with zero (and negative zero) components, in cell planes and on the cube's faces and edges."""
+    s = synth.random_tree_scene(4, 3, seed=5, p_split=0.6)
+    tree = core.Octree.from_scene(s)
+    tree.set_links(links)
+    at = np.array([-1.0, -0.75, -0.3, 0.0, 0.5, 0.7, 1.0])
+    o, d = [], []
+    for a in range(3):
+        for sgn in (1.0, -1.0):
+            for u in at:
+                for v in at:
+                    p = np.insert([u, v], a, -2.0 * sgn)
+                    q = np.full(3, -0.0)
+                    q[a] = sgn
+                    o.append(p)
+                    d.append(q)
+    # diagonals: several axes attain the exit at once
+    for sx in (1.0, -1.0):
+        for sy in (1.0, -1.0):
+            o.append([-2.0 * sx, -2.0 * sy, 0.25])
+            d.append([sx, sy, 0.0])
+            o.append([-2.0 * sx, -2.0 * sy, -2.0])
+            d.append([sx, sy, 1.0])
+    o, d = np.array(o, np.float32), np.array(d, np.float32)
+    rgb = tree.render(core.Rays.explicit(o, d), t_stop=0.0)
+    ref = O.render(O.OracleTree.from_scene(s, sigma=s.sigma.astype(np.float64)), o, d, t_stop=0.0)
+    assert np.abs(rgb.cpu().numpy() - ref["rgb"]).max() <= TOL32
+
+
+def test_tree_past_32bit_offsets():
+    """28.5M FP32 leaves of degree 3 (5.5 GB of rows), grown by refinement from 2.1M: subdividing a leaf does not
+    change the image, so it is the small tree's.  A ray crosses at most 3 * 2^9 + 64 leaves; each addition to the
+    optical depth S rounds by 2^-24 S and moves the colour by at most T S 2^-24 <= 2^-24 / e, each weighted colour
+    by 2^-24: 1600 * 2^-24 * (1 + 1/e) = 1.3e-4."""
+    s = synth.uniform_scene(7, 3, 0.4, seed=3)
+    tree = core.Octree.from_scene(s)
+    rays = core.Rays.cameras(synth.cameras([(30.0, 20.0, 4.0, 61, 45)]))
+    small = tree.render(rays, t_stop=0.0).cpu().numpy()
+    assert tree.info().sh_stride * 4 * tree.n_leaves < 2 ** 32
+    for frac in (1.0, 0.1):
+        tree.refine(torch.rand(tree.n_leaves, device="cuda") + 0.5, prune_tau=0.0, sample_frac=frac, max_depth=12)
+    assert tree.info().sh_stride * 4 * tree.n_leaves > 2 ** 32
+    for links in (True, False):
+        tree.set_links(links)
+        assert np.abs(tree.render(rays, t_stop=0.0).cpu().numpy() - small).max() <= 1.3e-4
