@@ -17,7 +17,7 @@ __global__ __launch_bounds__(BLOCK, FAR ? 1 : fwd_waves(DT, DEG)) void render_fw
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int64_t nb = gridDim.x;
-    const int64_t tile = xcd_block(blockIdx.x, nb) * WAVES_PER_BLOCK + __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t tile = xcd_tiles(blockIdx.x, nb, rb) * WAVES_PER_BLOCK + __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tile >= rb.n_tiles) return;
     Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
     int64_t rid = 0;

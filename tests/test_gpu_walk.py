@@ -75,3 +75,16 @@ def test_tree_past_32bit_offsets():
     for links in (True, False):
         tree.set_links(links)
         assert np.abs(tree.render(rays, t_stop=0.0).cpu().numpy() - small).max() <= 1.3e-4
+
+
+@pytest.mark.parametrize("views,w,h", [(1, 128, 63), (1, 128, 64), (1, 136, 72), (3, 77, 51), (8, 40, 33), (9, 64, 48)])
+def test_bands_cover_every_pixel(views, w, h):
+    """Whole views are handed to the XCDs in bands (63 to 65 workgroups: none, one tile row or a remainder); the same
+    pixels given as a list take another order."""
+    s = synth.random_tree_scene(4, 1, seed=9, p_split=0.5)
+    tree = core.Octree.from_scene(s)
+    cams = synth.random_sphere_cameras(views, 3.5, w, h, seed=views)
+    rgb = tree.render(core.Rays.cameras(cams))
+    i = np.arange(views * w * h)
+    listed = tree.render(core.Rays.pixels(cams, i // (w * h), i % (w * h)))
+    assert torch.equal(rgb, listed)
