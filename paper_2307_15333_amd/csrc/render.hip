@@ -9,10 +9,11 @@
 namespace dot {
 
 // MODE 0: plain; 1: with the traversal counters of dot_render_stats; 2: with
-// the per-leaf segment counts of a training forward.  FAR: a tree with a plane
+// the per-leaf segment counts of a training forward; 3: the signal alone (no
+// rows are fetched, so the kernel serves every degree).  FAR: a tree with a plane
 // past the reach of 32-bit offsets, walked lane by lane with 64-bit addresses.
 template <int DT, int DEG, int MODE, bool FAR>
-__global__ __launch_bounds__(BLOCK, FAR ? 1 : fwd_waves(DT, DEG)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
+__global__ __launch_bounds__(BLOCK, FAR ? 1 : MODE == 3 ? 6 : fwd_waves(DT, DEG)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
     __shared__ int stack_lds[LAT * BLOCK];
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
@@ -22,7 +23,7 @@ __global__ __launch_bounds__(BLOCK, FAR ? 1 : fwd_waves(DT, DEG)) void render_fw
     Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
     int64_t rid = 0;
     const bool live = make_ray(rb, tile, lane, r, rid);
-    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2>> seg(tv, a);
+    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2, MODE != 3>> seg(tv, a);
     seg.rid = rid;
     int desc = 0;
     seg.begin(r);
@@ -47,13 +48,13 @@ __global__ __launch_bounds__(BLOCK, FAR ? 1 : fwd_waves(DT, DEG)) void render_fw
             atomicAdd(a.rec.total, (uint32_t)seg.nrec);
         }
     }
-    if (a.rgb) {
+    if (MODE != 3 && a.rgb) {
         float Te = seg.T;
         a.rgb[3 * rid + 0] = fmaf(Te, a.bg[0], seg.C[0]);
         a.rgb[3 * rid + 1] = fmaf(Te, a.bg[1], seg.C[1]);
         a.rgb[3 * rid + 2] = fmaf(Te, a.bg[2], seg.C[2]);
     }
-    if (a.nseg) a.nseg[rid] = seg.n;
+    if (MODE != 3 && a.nseg) a.nseg[rid] = seg.n;
     if constexpr (MODE == 1) {
         atomicAdd(&a.stats[0], 1ull);
         atomicAdd(&a.stats[1], (unsigned long long)seg.n);
@@ -1088,6 +1089,10 @@ template <int DT>
 static hipError_t fwd_dispatch_reach(int deg, const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid,
                                      hipStream_t s) {
     if (!tv.near) return fwd_dispatch_deg<DT, true>(deg, tv, rb, a, grid, s);
+    if (!a.rgb && !a.nseg && !a.stats && !a.leaf_count) {
+        hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+        return hipGetLastError();
+    }
     return fwd_dispatch_deg<DT, false>(deg, tv, rb, a, grid, s);
 }
 

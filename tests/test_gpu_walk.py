@@ -88,3 +88,19 @@ def test_bands_cover_every_pixel(views, w, h):
     i = np.arange(views * w * h)
     listed = tree.render(core.Rays.pixels(cams, i // (w * h), i % (w * h)))
     assert torch.equal(rgb, listed)
+
+
+@pytest.mark.parametrize("storage,degree", [("f32", 3), ("f32", 0), ("f16", 2), ("bf16", 3)])
+@pytest.mark.parametrize("mode", ["max", "sum"])
+def test_signal_alone_equals_fused_signal(storage, degree, mode):
+    """The signal pass fetches no rows; its weights are the fused render's (the sum's order may differ)."""
+    s = synth.random_tree_scene(5, degree, seed=17, p_split=0.5)
+    tree = core.Octree.from_scene(s, storage)
+    rays = core.Rays.cameras(synth.random_sphere_cameras(3, 3.5, 45, 31, seed=2))
+    fused, alone = (torch.full((tree.n_leaves,), 0.25, device="cuda") for _ in range(2))
+    tree.render(rays, signal=fused, signal_mode=mode)
+    tree.accumulate_signal(rays, alone, signal_mode=mode)
+    if mode == "max":
+        assert torch.equal(fused, alone)
+    else:       # n additions of weights in [0, 1] in another order: n 2^-24 of the sum, n <= 4185 rays
+        torch.testing.assert_close(fused, alone, rtol=4185 * 2.0 ** -24, atol=0)
