@@ -444,4 +444,31 @@ __device__ __forceinline__ void walk_fwd(const TreeView& tv, const Ray& r, bool 
     }
 }
 
+// One ray per lane through the tree, by the walk that fits it; called by all
+// lanes of the wave.  LINKED: the caller knows that the tree is near and has
+// links (the other walks are then not compiled in).
+template <class Wave, class Lane, bool LINKED>
+__device__ __forceinline__ void trace_pixel(const TreeView& tv, const FwdArgs& a, const Ray& r, bool live,
+                                            int* __restrict__ stk, const float (&bg)[3], float (&rgb)[3]) {
+    int desc = 0;
+    auto out = [&](const auto& seg) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) rgb[c] = fmaf(seg.T, bg[c], seg.C[c]);
+    };
+    if (LINKED || tv.near) {
+        Wave seg(tv, a);
+        seg.begin(r);
+        if (LINKED || tv.links)
+            walk_fwd<true>(tv, r, live, stk, seg, desc);
+        else
+            walk_fwd<false>(tv, r, live, stk, seg, desc);
+        out(seg);
+    } else {
+        Lane seg(tv, a);
+        seg.begin(r);
+        if (live) traverse(tv, r, stk, seg, desc);
+        out(seg);
+    }
+}
+
 }  // namespace dot

@@ -49,7 +49,7 @@
 #include <cstring>
 #include <vector>
 
-#include "dot_device.h"
+#include "fwd_walk.h"
 
 namespace dot {
 
@@ -313,24 +313,23 @@ __device__ __forceinline__ void serve_tile(const ServeJob& j, int64_t t, int lan
     const int tw = (j.width + 7) >> 3;
     const int ty = (int)(t / tw), tx = (int)(t - (int64_t)ty * tw);
     const int u = tx * 8 + (lane & 7), v = ty * 8 + (lane >> 3);
-    if (u >= j.width || v >= j.height) return;
-    Ray r = camera_ray(j.cam, u, v);
+    const bool live = u < j.width && v < j.height;
+    const Ray r = camera_ray(j.cam, u, v);
     FwdArgs a{};
     a.thr = j.thr;
-    FwdSeg<DT, DEG> seg(j.tv, a);
-    sh_basis<DEG>((float)r.dx, (float)r.dy, (float)r.dz, seg.Y);
-    int desc = 0;
-    traverse(j.tv, r, stk, seg, desc);
+    float rgb[3];
+    trace_pixel<FwdWave<DT, DEG>, FwdSeg<DT, DEG>, false>(j.tv, a, r, live, stk, j.bg, rgb);
+    if (!live) return;
     // device-scope stores: written through to where every XCD (and a copy
     // engine) sees them, so completing them is all the publication needs
     float* o = j.rgb + 3 * ((int64_t)v * j.width + u);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-        __hip_atomic_store(o + c, fmaf(seg.T, j.bg[c], seg.C[c]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(o + c, rgb[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int DT>
-__global__ __launch_bounds__(BLOCK) void serve_loop_kernel(ServeHostCtl* ctl, const ServeJob* hjobs, uint64_t* hdone,
+__global__ __launch_bounds__(BLOCK, 4) void serve_loop_kernel(ServeHostCtl* ctl, const ServeJob* hjobs, uint64_t* hdone,
                                                            ServeDevice dv, int max_jobs, uint64_t limit_ticks) {
     __shared__ int stack_lds[LAT * BLOCK];   // the walk's ancestor stacks; the feeder's chunk cursors
     static_assert(LAT * BLOCK >= WAVE * kRings, "feeder cursors fit in the stack array");

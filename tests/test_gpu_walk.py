@@ -104,3 +104,22 @@ def test_signal_alone_equals_fused_signal(storage, degree, mode):
         assert torch.equal(fused, alone)
     else:       # n additions of weights in [0, 1] in another order: n 2^-24 of the sum, n <= 4185 rays
         torch.testing.assert_close(fused, alone, rtol=4185 * 2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("links", [(True, True), (True, False)])
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_jobs_batch_equals_render(storage, links):
+    """A batch of jobs, down to a single tile, over trees that all have links and over a mix (another kernel)."""
+    from paper_2307_15333_amd import serve
+    trees = []
+    for k, on in enumerate(links):
+        t = core.Octree.from_scene(synth.random_tree_scene(5, 3 - k, seed=40 + k, p_split=0.5), storage)
+        t.set_links(on)
+        trees.append(t)
+    for sizes in ([(7, 5)], [(64, 40), (9, 200), (33, 31), (128, 8)]):
+        reqs = [serve.Request(rid=i, tree=i % 2, cam=synth.cameras([(40.0 * i, 10.0, 4.0, w, h)])[0], width=w, height=h,
+                              arrival=0.0) for i, (w, h) in enumerate(sizes)]
+        serve.Server(trees).run(reqs, keep_outputs=True)
+        for r in reqs:
+            want = trees[r.tree].render(core.Rays.cameras(np.array([r.cam])))
+            assert torch.equal(r.out.reshape(-1, 3), want)
