@@ -130,6 +130,7 @@ __global__ void k_keys(const float* __restrict__ sig, const uint8_t* __restrict_
 struct SelState {
     unsigned long long prefix, mask;
     unsigned long long k_rem, k_eff;
+    unsigned int deepest;      // depth of the refined tree's deepest leaf
     unsigned int hist[256];
 };
 
@@ -140,6 +141,7 @@ __global__ void k_sel_init(SelState* st) {
         st->mask = 0;
         st->k_rem = 0;
         st->k_eff = 0;
+        st->deepest = 0;
     }
     st->hist[t] = 0;
 }
@@ -183,8 +185,10 @@ __global__ void k_sel_digit(SelState* st, int shift, int first, long long k_req)
 
 // new-leaf counts per old leaf, and the split flags
 __global__ void k_leaf_counts(int64_t L, const int32_t* __restrict__ cover, const int32_t* __restrict__ first,
-                              const uint64_t* __restrict__ keys, const SelState* __restrict__ st,
+                              const uint64_t* __restrict__ keys, const uint8_t* __restrict__ depth,
+                              const int32_t* __restrict__ ndepth, SelState* __restrict__ st,
                               uint32_t* __restrict__ cnt, uint32_t* __restrict__ split) {
+    unsigned int d = 0u;
     const unsigned long long kstar = st->prefix;
     const bool any = st->k_eff > 0;
     GRID_STRIDE(l, L) {
@@ -192,7 +196,11 @@ __global__ void k_leaf_counts(int64_t L, const int32_t* __restrict__ cover, cons
         bool sp = any && keys[l] != ~0ull && keys[l] <= kstar;
         split[l] = sp ? 1u : 0u;
         cnt[l] = c >= 0 ? (first[c] == (int32_t)l ? 1u : 0u) : (sp ? 8u : 1u);
+        d = max(d, c >= 0 ? (unsigned int)ndepth[c] : depth[l] + (sp ? 1u : 0u));
     }
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) d = max(d, (unsigned int)__shfl_xor((int)d, o, WAVE));
+    if ((threadIdx.x & (WAVE - 1)) == 0 && d > st->deepest) atomicMax(&st->deepest, d);
 }
 
 __global__ void k_add_u32(uint32_t* __restrict__ a, const uint32_t* __restrict__ h, int64_t n) {
@@ -271,82 +279,96 @@ __device__ __forceinline__ void st_elem(void* p, int64_t i, double x) {
     }
 }
 
-template <int DT>
-__device__ __forceinline__ void cp_elem(const void* src, int64_t i, void* dst, int64_t j) {
-    if constexpr (DT == DOT_F32)
-        static_cast<float*>(dst)[j] = static_cast<const float*>(src)[i];
-    else
-        static_cast<uint16_t*>(dst)[j] = static_cast<const uint16_t*>(src)[i];
-}
+// Rows move in 16-byte pieces, one thread a piece, so that a wave reads and
+// writes whole lines (a thread a row touched a line per lane and instruction:
+// 2.0 ms for the rows of a 3.5M-leaf tree of degree 3, 0.4 ms so).
 
-// Values of merged nodes, one depth level per launch from the deepest up: the
-// mean of the 8 children's rows (leaf rows, or node rows formed by the previous
-// launch), summed pairwise in FP64 and rounded once to the storage type.
-// Row layout of nval: [sigma, sh[0..stride)] per node, in the storage type.
+// Values of merged nodes: the mean of the 8 children's rows (leaf rows, or node
+// rows formed by the previous launch), summed pairwise in FP64 and rounded once
+// to the storage type.  depth < 0: every merged node (its children are leaves);
+// else those of one level, launched from the deepest up.
 template <int DT>
-__global__ void k_node_values(const int32_t* __restrict__ child, int64_t I, int depth,
-                              const int32_t* __restrict__ ndepth, const uint32_t* __restrict__ need, int nv,
-                              int stride, const void* __restrict__ sig, const void* __restrict__ sh,
-                              void* __restrict__ nval) {
-    const int row = stride + 1;
-    GRID_STRIDE(p, I) {
-        if (!need[p] || ndepth[p] != depth) continue;
+__global__ __launch_bounds__(TPB) void k_node_values(const int32_t* __restrict__ child, int64_t I, int depth,
+                                                     const int32_t* __restrict__ ndepth,
+                                                     const uint32_t* __restrict__ need, int nv, int pieces,
+                                                     const void* __restrict__ sig, const uint4* __restrict__ sh,
+                                                     void* __restrict__ nsig, uint4* __restrict__ nsh) {
+    constexpr int E = DT == DOT_F32 ? 4 : 8;      // elements per piece
+    union Piece {
+        uint4 v;
+        float f[4];
+        uint16_t h[8];
+    };
+    GRID_STRIDE(i, I * pieces) {
+        const int64_t p = i / pieces;
+        const int q = (int)(i - p * pieces);
+        if (!need[p] || (depth >= 0 && ndepth[p] != depth)) continue;
         int32_t e[8];
+        Piece x[8], m;
 #pragma unroll
         for (int o = 0; o < 8; ++o) e[o] = child[p * 8 + o];
-        for (int c = -1; c < nv; ++c) {
-            double v[8];
 #pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                if (e[o] < 0) {
-                    int64_t l = -1 - e[o];
-                    v[o] = c < 0 ? ld_elem<DT>(sig, l) : ld_elem<DT>(sh, l * stride + c);
-                } else {
-                    v[o] = ld_elem<DT>(nval, (int64_t)e[o] * row + 1 + c);
-                }
-            }
-            double m = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * 0.125;
-            st_elem<DT>(nval, p * row + 1 + c, m);
-        }
-        for (int c = nv; c < stride; ++c) st_elem<DT>(nval, p * row + 1 + c, 0.0);
+        for (int o = 0; o < 8; ++o) x[o].v = e[o] < 0 ? sh[(int64_t)(-1 - e[o]) * pieces + q] : nsh[(int64_t)e[o] * pieces + q];
+        auto mean = [&](auto at) {
+            return (((at(0) + at(1)) + (at(2) + at(3))) + ((at(4) + at(5)) + (at(6) + at(7)))) * 0.125;
+        };
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            st_elem<DT>(&m, k, q * E + k < nv ? mean([&](int o) { return ld_elem<DT>(&x[o], k); }) : 0.0);
+        nsh[i] = m.v;
+        if (q == 0)
+            st_elem<DT>(nsig, p, mean([&](int o) {
+                return e[o] < 0 ? ld_elem<DT>(sig, -1 - e[o]) : ld_elem<DT>(nsig, (int64_t)e[o]);
+            }));
     }
 }
 
-template <int DT>
-__global__ void k_emit_leaves(int64_t L, int stride, int reinit, const int32_t* __restrict__ cover,
-                              const int32_t* __restrict__ first, const int32_t* __restrict__ ndepth,
-                              const uint32_t* __restrict__ split, const uint32_t* __restrict__ nl,
-                              const uint8_t* __restrict__ depth, const void* __restrict__ sig,
-                              const void* __restrict__ sh, const void* __restrict__ nval, void* __restrict__ sig2,
-                              void* __restrict__ sh2, uint8_t* __restrict__ depth2) {
-    const int row = stride + 1;
+// where each new leaf's row comes from: an old leaf (>= 0), or merged node -1 - n
+__global__ void k_sources(int64_t L, const int32_t* __restrict__ cover, const int32_t* __restrict__ first,
+                          const uint32_t* __restrict__ split, const uint32_t* __restrict__ nl,
+                          int32_t* __restrict__ src) {
     GRID_STRIDE(l, L) {
-        int32_t c = cover[l];
-        int64_t j = nl[l];
+        const int32_t c = cover[l];
+        const int64_t j = nl[l];
         if (c >= 0) {
-            if (first[c] != (int32_t)l) continue;
-            if (reinit) {
-                st_elem<DT>(sig2, j, 0.0);
-                for (int k = 0; k < stride; ++k) st_elem<DT>(sh2, j * stride + k, 0.0);
-            } else {
-                cp_elem<DT>(nval, (int64_t)c * row, sig2, j);
-                for (int k = 0; k < stride; ++k) cp_elem<DT>(nval, (int64_t)c * row + 1 + k, sh2, j * stride + k);
-            }
-            depth2[j] = (uint8_t)ndepth[c];
+            if (first[c] == (int32_t)l) src[j] = -1 - c;
         } else {
-            int reps = split[l] ? 8 : 1;
-            uint8_t d = (uint8_t)(depth[l] + (split[l] ? 1 : 0));
-            for (int r = 0; r < reps; ++r) {
-                if (reinit && split[l]) {
-                    st_elem<DT>(sig2, j + r, 0.0);
-                    for (int k = 0; k < stride; ++k) st_elem<DT>(sh2, (j + r) * stride + k, 0.0);
-                } else {
-                    cp_elem<DT>(sig, l, sig2, j + r);
-                    for (int k = 0; k < stride; ++k) cp_elem<DT>(sh, l * stride + k, sh2, (j + r) * stride + k);
-                }
-                depth2[j + r] = d;
-            }
+            const int reps = split[l] ? 8 : 1;
+            for (int r = 0; r < reps; ++r) src[j + r] = (int32_t)l;
         }
+    }
+}
+
+constexpr int EMIT_ROWS = 64;    // new leaves per workgroup
+
+template <int DT>
+__global__ __launch_bounds__(TPB) void k_emit_rows(int64_t L2, int pieces, int reinit, const int32_t* __restrict__ src,
+                                                   const uint32_t* __restrict__ split,
+                                                   const int32_t* __restrict__ ndepth,
+                                                   const uint8_t* __restrict__ depth, const void* __restrict__ sig,
+                                                   const uint4* __restrict__ sh, const void* __restrict__ nsig,
+                                                   const uint4* __restrict__ nsh, void* __restrict__ sig2,
+                                                   uint4* __restrict__ sh2, uint8_t* __restrict__ depth2) {
+    const int64_t j0 = (int64_t)blockIdx.x * EMIT_ROWS;
+    const int rows = (int)(L2 - j0 < EMIT_ROWS ? L2 - j0 : EMIT_ROWS);
+    const uint32_t n = (uint32_t)(rows * pieces);
+    uint4* out = sh2 + j0 * pieces;
+#pragma unroll 4
+    for (uint32_t t = threadIdx.x; t < n; t += TPB) {
+        const uint32_t r = t / (uint32_t)pieces, q = t - r * (uint32_t)pieces;
+        const int64_t s = src[j0 + r];
+        // a leaf the refinement creates starts at zero in the ablation without fusion
+        const bool fresh = reinit && (s < 0 || split[s]);
+        out[t] = fresh ? make_uint4(0u, 0u, 0u, 0u) : s < 0 ? nsh[(-1 - s) * pieces + q] : sh[s * pieces + q];
+    }
+    for (int r = threadIdx.x; r < rows; r += TPB) {
+        const int64_t j = j0 + r, s = src[j];
+        const bool cut = s >= 0 && split[s];
+        if (reinit && (s < 0 || cut))
+            st_elem<DT>(sig2, j, 0.0);
+        else
+            st_elem<DT>(sig2, j, s < 0 ? ld_elem<DT>(nsig, -1 - s) : ld_elem<DT>(sig, s));
+        depth2[j] = s < 0 ? (uint8_t)ndepth[-1 - s] : (uint8_t)(depth[s] + (cut ? 1 : 0));
     }
 }
 
@@ -358,6 +380,7 @@ __global__ void k_totals(int64_t L, int64_t I, const uint32_t* __restrict__ nl, 
     out[1] = (unsigned long long)(I > 0 ? *tot_int : 0u) + *tot_split;  // new internal nodes
     out[2] = (unsigned long long)(I > 0 ? (uint64_t)I - *tot_int : 0u);  // merged nodes
     out[3] = st->k_eff;
+    out[4] = st->deepest;
 }
 
 // RAII list of temporaries from the tree's allocator
@@ -379,18 +402,25 @@ struct Temps {
 };
 
 template <int DT>
-hipError_t launch_values_emit(const dot_tree& t, int64_t L, int64_t I, int nv, int stride, int reinit,
-                              const int32_t* cover,
-                              const int32_t* first, const int32_t* ndepth, const uint32_t* need,
-                              const uint32_t* split, const uint32_t* nl, void* nval, void* sig2, void* sh2,
-                              uint8_t* depth2, hipStream_t s) {
-    if (I > 0)
-        for (int d = DOT_MAX_DEPTH - 1; d >= 0; --d)
-            hipLaunchKernelGGL(k_node_values<DT>, dim3(blocks_for(I)), dim3(TPB), 0, s, t.child, I, d, ndepth, need,
-                               nv, stride, t.sigma, t.sh, nval);
-    hipLaunchKernelGGL(k_emit_leaves<DT>, dim3(blocks_for(L)), dim3(TPB), 0, s, L, stride, reinit, cover, first, ndepth,
-                       split,
-                       nl, t.leaf_depth, t.sigma, t.sh, nval, sig2, sh2, depth2);
+hipError_t launch_values_emit(const dot_tree& t, int64_t L2, int64_t I, int nv, const dot_refine_params& p,
+                              const int32_t* ndepth, const uint32_t* need, const uint32_t* split, const int32_t* src,
+                              void* nsig, void* nsh, void* sig2, void* sh2, uint8_t* depth2, hipStream_t s) {
+    const int pieces = t.sh_stride * storage_bytes(t.storage) / 16;
+    const uint4* sh = static_cast<const uint4*>(t.sh);
+    uint4* vsh = static_cast<uint4*>(nsh);
+    auto values = [&](int depth) {
+        hipLaunchKernelGGL(k_node_values<DT>, dim3(blocks_for(I * pieces)), dim3(TPB), 0, s, t.child, I, depth, ndepth,
+                           need, nv, pieces, t.sigma, sh, nsig, vsh);
+    };
+    if (I > 0 && !p.reinit) {
+        if (p.recursive)
+            for (int d = std::min(t.max_depth, DOT_MAX_DEPTH) - 1; d >= 0; --d) values(d);
+        else
+            values(-1);
+    }
+    hipLaunchKernelGGL(k_emit_rows<DT>, dim3((unsigned)((L2 + EMIT_ROWS - 1) / EMIT_ROWS)), dim3(TPB), 0, s, L2, pieces,
+                       p.reinit, src, split, ndepth, t.leaf_depth, t.sigma, sh, nsig, vsh, sig2,
+                       static_cast<uint4*>(sh2), depth2);
     return hipGetLastError();
 }
 
@@ -416,7 +446,8 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     uint32_t* root = tmp.get<uint32_t>(I);
     uint32_t* need = tmp.get<uint32_t>(I);
     uint32_t* rank_int = tmp.get<uint32_t>(I);
-    void* nval = tmp.get<unsigned char>(std::max<int64_t>(I, 1) * (stride + 1) * es);
+    void* nsh = tmp.get<unsigned char>(std::max<int64_t>(I, 1) * stride * es);
+    void* nsig = tmp.get<unsigned char>(std::max<int64_t>(I, 1) * es);
     uint32_t* unsel = tmp.get<uint32_t>(L);
     uint32_t* pre_unsel = tmp.get<uint32_t>(L);
     int32_t* cover = tmp.get<int32_t>(L);
@@ -430,7 +461,7 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     uint32_t* cnt_le = tmp.get<uint32_t>(L);
     uint32_t* bsum = tmp.get<uint32_t>(scan_scratch_elems(std::max(L, I)));
     uint32_t* tots = tmp.get<uint32_t>(8);
-    unsigned long long* totals = tmp.get<unsigned long long>(4);
+    unsigned long long* totals = tmp.get<unsigned long long>(5);
     if (!tmp.ok) return fail(DOT_ENOMEM, "dot_refine: scratch allocation failed");
 
     // 1. tree metadata, merge marks, candidate keys
@@ -464,7 +495,8 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
         }
     }
     // 3. counts and scans
-    hipLaunchKernelGGL(k_leaf_counts, dim3(blocks_for(L)), dim3(TPB), 0, s, L, cover, first, keys, sel, cnt, split);
+    hipLaunchKernelGGL(k_leaf_counts, dim3(blocks_for(L, 8)), dim3(TPB), 0, s, L, cover, first, keys,
+                       t.leaf_depth, ndepth, sel, cnt, split);
     if (I > 0) hipLaunchKernelGGL(k_first_hist, dim3(blocks_for(I)), dim3(TPB), 0, s, I, survive, first, hist_first);
     e = scan_u32(cnt, nl, L, bsum, &tots[0], s);
     if (e == hipSuccess) e = scan_u32(split, rank_split, L, bsum, &tots[1], s);
@@ -474,7 +506,7 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     // cnt_le becomes inclusive: surviving nodes whose first leaf is <= l
     hipLaunchKernelGGL(k_add_u32, dim3(blocks_for(L)), dim3(TPB), 0, s, cnt_le, (const uint32_t*)hist_first, L);
     hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, s, L, I, nl, cnt, &tots[3], &tots[1], sel, totals);
-    unsigned long long h_tot[4];
+    unsigned long long h_tot[5];
     e = hipMemcpyAsync(h_tot, totals, sizeof(h_tot), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "dot_refine: sizes");
@@ -485,13 +517,14 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     void* sig2 = t.alloc.get((size_t)L2 * es);
     void* sh2 = t.alloc.get((size_t)L2 * stride * es);
     uint8_t* depth2 = static_cast<uint8_t*>(t.alloc.get((size_t)L2));
+    int32_t* src = tmp.get<int32_t>(L2);
     auto drop_new = [&]() {
         t.alloc.put(child2);
         t.alloc.put(sig2);
         t.alloc.put(sh2);
         t.alloc.put(depth2);
     };
-    if (!child2 || !sig2 || !sh2 || !depth2) {
+    if (!child2 || !sig2 || !sh2 || !depth2 || !src) {
         drop_new();
         return fail(DOT_ENOMEM, "dot_refine: allocation of the refined planes failed");
     }
@@ -499,15 +532,13 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
         hipLaunchKernelGGL(k_child_internal, dim3(blocks_for(I)), dim3(TPB), 0, s, t.child, I, survive, first,
                            rank_int, rank_split, split, cnt_le, nl, child2);
     hipLaunchKernelGGL(k_child_split, dim3(blocks_for(L)), dim3(TPB), 0, s, L, split, rank_split, cnt_le, nl, child2);
-    if (t.storage == DOT_F32)
-        e = launch_values_emit<DOT_F32>(t, L, I, nv, stride, p.reinit, cover, first, ndepth, need, split, nl, nval, sig2, sh2,
-                                        depth2, s);
-    else if (t.storage == DOT_F16)
-        e = launch_values_emit<DOT_F16>(t, L, I, nv, stride, p.reinit, cover, first, ndepth, need, split, nl, nval, sig2, sh2,
-                                        depth2, s);
-    else
-        e = launch_values_emit<DOT_BF16>(t, L, I, nv, stride, p.reinit, cover, first, ndepth, need, split, nl, nval, sig2, sh2,
-                                         depth2, s);
+    hipLaunchKernelGGL(k_sources, dim3(blocks_for(L)), dim3(TPB), 0, s, L, cover, first, split, nl, src);
+    auto emit = [&](auto launch) {
+        return launch(t, L2, I, nv, p, ndepth, need, split, src, nsig, nsh, sig2, sh2, depth2, s);
+    };
+    e = t.storage == DOT_F32   ? emit(launch_values_emit<DOT_F32>)
+        : t.storage == DOT_F16 ? emit(launch_values_emit<DOT_F16>)
+                               : emit(launch_values_emit<DOT_BF16>);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         drop_new();
@@ -524,8 +555,7 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     t.leaf_depth = depth2;
     t.n_leaves = L2;
     t.n_internal = I2;
-    // an upper bound on the deepest leaf (it only bounds traversal steps)
-    t.max_depth = std::min(DOT_MAX_DEPTH, t.max_depth + (h_tot[3] > 0 ? 1 : 0));
+    t.max_depth = (int32_t)h_tot[4];   // bounds the walk's steps and the levels of the links
     if (st_out) {
         st_out->leaves_before = L;
         st_out->leaves_after = L2;
