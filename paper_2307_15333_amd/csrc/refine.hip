@@ -8,8 +8,8 @@
 //           selected merged: the subtree's leaves are a contiguous DFS range,
 //           so one prefix count of unselected leaves decides every node;
 //   select  exact top-k of the 64-bit keys (~ord(signal) << 32 | leaf) over
-//           the sampling candidates by an 8-pass MSD radix select, so ties in
-//           signal go to the lower leaf index;
+//           the sampling candidates by an MSD radix select of up to 6 digits,
+//           so ties in signal go to the lower leaf index;
 //   rebuild new leaf and internal indices by exclusive prefix scans over the
 //           old DFS order, then scatter: a merged group becomes one leaf with
 //           the mean of its 8 rows (Eq. 3), a sampled leaf becomes an internal
@@ -76,8 +76,19 @@ __global__ void k_node_parent(const int32_t* __restrict__ child, int64_t I, int3
     }
 }
 
-__global__ void k_unselected(const float* __restrict__ sig, int64_t L, float tau, int le, uint32_t* __restrict__ u) {
-    GRID_STRIDE(l, L) u[l] = selected(sig[l], tau, le) ? 0u : 1u;
+// everything a leaf starts with: whether it is left unselected by the pruning,
+// its sampling key (all ones: not a candidate), no covering root, no node count
+__global__ void k_leaf_init(const float* __restrict__ sig, const uint8_t* __restrict__ depth, int64_t L, float tau, int le,
+                            int max_depth, uint32_t* __restrict__ u, uint64_t* __restrict__ keys,
+                            int32_t* __restrict__ cover, uint32_t* __restrict__ hist_first) {
+    GRID_STRIDE(l, L) {
+        const float s = sig[l];
+        const bool sel = selected(s, tau, le);
+        u[l] = sel ? 0u : 1u;
+        keys[l] = !sel && (int)depth[l] < max_depth ? (((uint64_t)(~ord32(s)) << 32) | (uint64_t)l) : ~0ull;
+        cover[l] = -1;
+        hist_first[l] = 0u;
+    }
 }
 
 // merge roots and survivors.  all_sel[p]: no unselected leaf in [first, last].
@@ -118,76 +129,100 @@ __global__ void k_cover(int64_t I, const uint32_t* __restrict__ root, const int3
     }
 }
 
-__global__ void k_keys(const float* __restrict__ sig, const uint8_t* __restrict__ depth, int64_t L, float tau,
-                       int le, int max_depth, uint64_t* __restrict__ keys) {
-    GRID_STRIDE(l, L) {
-        float s = sig[l];
-        bool cand = !selected(s, tau, le) && (int)depth[l] < max_depth;
-        keys[l] = cand ? (((uint64_t)(~ord32(s)) << 32) | (uint64_t)l) : ~0ull;
-    }
-}
+constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS;
 
 struct SelState {
     unsigned long long prefix, mask;
     unsigned long long k_rem, k_eff;
-    unsigned int deepest;      // depth of the refined tree's deepest leaf
-    unsigned int hist[256];
+    unsigned int done;         // the digits found so far decide every key
+    unsigned int ticket;       // workgroups of the current pass that are through
+    unsigned int hist[SEL_BINS];
 };
 
-__global__ void k_sel_init(SelState* st) {
-    int t = threadIdx.x;
-    if (t == 0) {
-        st->prefix = 0;
-        st->mask = 0;
-        st->k_rem = 0;
-        st->k_eff = 0;
-        st->deepest = 0;
-    }
-    st->hist[t] = 0;
+// a word written by other workgroups' atomics of this launch
+__device__ __forceinline__ unsigned int read_shared_word(unsigned int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_hist(const uint64_t* __restrict__ keys, int64_t L, int shift, SelState* st) {
-    __shared__ unsigned int h[256];
-    h[threadIdx.x] = 0;
+// One digit of the radix select: the histogram of the candidates that match the
+// digits so far, then, in the last workgroup to finish, the digit holding the
+// k_rem-th smallest.  When that digit's bin holds just the keys still wanted,
+// every key is decided and the later passes return at once (distinct signals
+// take three or four passes of six; each pass cost two launches and a serial
+// walk of the bins before, 0.20 ms per selection from 3.5M keys in all).
+__global__ __launch_bounds__(TPB) void k_select(const uint64_t* __restrict__ keys, int64_t L, int shift, int bits, int first,
+                                                unsigned long long k_req, SelState* st) {
+    __shared__ unsigned int h[SEL_BINS];
+    __shared__ unsigned long long part[TPB];
+    __shared__ int last;
+    if (!first && st->done) return;
+    const unsigned int bins = 1u << bits;
+    for (unsigned int i = threadIdx.x; i < bins; i += TPB) h[i] = 0;
     __syncthreads();
     const unsigned long long prefix = st->prefix, mask = st->mask;
     GRID_STRIDE(l, L) {
-        uint64_t k = keys[l];
-        if (k != ~0ull && (k & mask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1u);
+        const uint64_t k = keys[l];
+        if (k != ~0ull && (k & mask) == prefix) atomicAdd(&h[(k >> shift) & (bins - 1u)], 1u);
     }
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
-}
-
-// one thread: choose the digit holding the k_rem-th smallest candidate
-__global__ void k_sel_digit(SelState* st, int shift, int first, long long k_req) {
-    if (threadIdx.x != 0) return;
-    if (first) {
-        unsigned long long n = 0;
-        for (int d = 0; d < 256; ++d) n += st->hist[d];
-        unsigned long long k = (unsigned long long)k_req < n ? (unsigned long long)k_req : n;
-        st->k_eff = k;
-        st->k_rem = k;
+    for (unsigned int i = threadIdx.x; i < bins; i += TPB)
+        if (h[i]) atomicAdd(&st->hist[i], h[i]);
+    // this wave's additions are complete before the workgroup's ticket is drawn
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&st->ticket, 1u) == gridDim.x - 1u;
+    __syncthreads();
+    if (!last) return;
+    // each thread a run of bins, the runs' sums scanned
+    const unsigned int per = bins / TPB;
+    unsigned long long run = 0;
+    for (unsigned int i = 0; i < per; ++i) run += read_shared_word(&st->hist[threadIdx.x * per + i]);
+    part[threadIdx.x] = run;
+    __syncthreads();
+    for (int o = 1; o < TPB; o <<= 1) {
+        const unsigned long long y = (int)threadIdx.x >= o ? part[threadIdx.x - o] : 0ull;
+        __syncthreads();
+        part[threadIdx.x] += y;
+        __syncthreads();
     }
-    if (st->k_rem > 0) {
-        unsigned long long cum = 0;
-        int d = 0;
-        for (; d < 256; ++d) {
-            if (cum + st->hist[d] >= st->k_rem) break;
-            cum += st->hist[d];
+    unsigned long long want = st->k_rem;
+    if (first) want = k_req < part[TPB - 1] ? k_req : part[TPB - 1];
+    const unsigned long long before = part[threadIdx.x] - run;
+    __syncthreads();
+    if (want == 0) {
+        if (threadIdx.x == 0) {
+            st->k_eff = 0;
+            st->done = 1;
         }
-        st->k_rem -= cum;
-        st->prefix |= (unsigned long long)d << shift;
-        st->mask |= 255ull << shift;
+    } else if (before < want && want <= before + run) {
+        unsigned long long cum = before;
+        unsigned int d = threadIdx.x * per, c = 0;
+        while (cum + (c = read_shared_word(&st->hist[d])) < want) {
+            cum += c;
+            ++d;
+        }
+        unsigned long long p = prefix | ((unsigned long long)d << shift);
+        if (c == want - cum) {
+            p |= (1ull << shift) - 1ull;      // the whole bin
+            st->done = 1;
+        }
+        if (first) st->k_eff = want;
+        st->k_rem = want - cum;
+        st->prefix = p;
+        st->mask = mask | ((unsigned long long)(bins - 1u) << shift);
     }
-    for (int d = 0; d < 256; ++d) st->hist[d] = 0;
+    __syncthreads();
+    for (unsigned int i = threadIdx.x; i < SEL_BINS; i += TPB) st->hist[i] = 0;
+    if (threadIdx.x == 0) st->ticket = 0;
 }
 
-// new-leaf counts per old leaf, and the split flags
+// new-leaf counts per old leaf, the split flags, and the deepest new leaf of
+// each workgroup's part
 __global__ void k_leaf_counts(int64_t L, const int32_t* __restrict__ cover, const int32_t* __restrict__ first,
                               const uint64_t* __restrict__ keys, const uint8_t* __restrict__ depth,
-                              const int32_t* __restrict__ ndepth, SelState* __restrict__ st,
-                              uint32_t* __restrict__ cnt, uint32_t* __restrict__ split) {
+                              const int32_t* __restrict__ ndepth, const SelState* __restrict__ st,
+                              uint32_t* __restrict__ cnt, uint32_t* __restrict__ split, uint32_t* __restrict__ deep) {
+    __shared__ uint32_t part[TPB / WAVE];
     unsigned int d = 0u;
     const unsigned long long kstar = st->prefix;
     const bool any = st->k_eff > 0;
@@ -200,7 +235,12 @@ __global__ void k_leaf_counts(int64_t L, const int32_t* __restrict__ cover, cons
     }
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) d = max(d, (unsigned int)__shfl_xor((int)d, o, WAVE));
-    if ((threadIdx.x & (WAVE - 1)) == 0 && d > st->deepest) atomicMax(&st->deepest, d);
+    if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x / WAVE] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < TPB / WAVE; ++w) d = max(d, part[w]);
+        deep[blockIdx.x] = d;
+    }
 }
 
 __global__ void k_add_u32(uint32_t* __restrict__ a, const uint32_t* __restrict__ h, int64_t n) {
@@ -220,27 +260,26 @@ __global__ void k_child_internal(const int32_t* __restrict__ child, int64_t I, c
                                  const uint32_t* __restrict__ rank_split, const uint32_t* __restrict__ split,
                                  const uint32_t* __restrict__ cnt_le, const uint32_t* __restrict__ nl,
                                  int32_t* __restrict__ out) {
-    GRID_STRIDE(p, I) {
+    // a thread an entry: the entries of a node, and the leaves they name, lie together
+    GRID_STRIDE(i, I * 8) {
+        const int64_t p = i >> 3;
         if (!survive[p]) continue;
-        int64_t np = (int64_t)rank_int[p] + rank_split[first[p]];
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-            int32_t e = child[p * 8 + o];
-            int32_t v;
-            if (e >= 0) {
-                if (survive[e])
-                    v = (int32_t)(rank_int[e] + rank_split[first[e]]);
-                else
-                    v = -1 - (int32_t)nl[first[e]];
-            } else {
-                int64_t l = -1 - e;
-                if (split[l])
-                    v = (int32_t)(rank_split[l] + cnt_le[l]);
-                else
-                    v = -1 - (int32_t)nl[l];
-            }
-            out[np * 8 + o] = v;
+        const int64_t np = (int64_t)rank_int[p] + rank_split[first[p]];
+        const int32_t e = child[i];
+        int32_t v;
+        if (e >= 0) {
+            if (survive[e])
+                v = (int32_t)(rank_int[e] + rank_split[first[e]]);
+            else
+                v = -1 - (int32_t)nl[first[e]];
+        } else {
+            const int64_t l = -1 - e;
+            if (split[l])
+                v = (int32_t)(rank_split[l] + cnt_le[l]);
+            else
+                v = -1 - (int32_t)nl[l];
         }
+        out[np * 8 + (i & 7)] = v;
     }
 }
 
@@ -300,7 +339,8 @@ __global__ __launch_bounds__(TPB) void k_node_values(const int32_t* __restrict__
         uint16_t h[8];
     };
     GRID_STRIDE(i, I * pieces) {
-        const int64_t p = i / pieces;
+        // I <= 2^28 and at most 12 pieces a row: 32-bit division
+        const int64_t p = (uint32_t)i / (uint32_t)pieces;
         const int q = (int)(i - p * pieces);
         if (!need[p] || (depth >= 0 && ndepth[p] != depth)) continue;
         int32_t e[8];
@@ -374,13 +414,18 @@ __global__ __launch_bounds__(TPB) void k_emit_rows(int64_t L2, int pieces, int r
 
 __global__ void k_totals(int64_t L, int64_t I, const uint32_t* __restrict__ nl, const uint32_t* __restrict__ cnt,
                          const uint32_t* __restrict__ tot_int, const uint32_t* __restrict__ tot_split,
-                         const SelState* __restrict__ st, unsigned long long* __restrict__ out) {
+                         const SelState* __restrict__ st, const uint32_t* __restrict__ deep, int n_deep,
+                         unsigned long long* __restrict__ out) {
+    uint32_t d = 0u;
+    for (int i = threadIdx.x; i < n_deep; i += WAVE) d = max(d, deep[i]);
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) d = max(d, (uint32_t)__shfl_xor((int)d, o, WAVE));
     if (threadIdx.x != 0) return;
     out[0] = (unsigned long long)nl[L - 1] + cnt[L - 1];      // new leaves
     out[1] = (unsigned long long)(I > 0 ? *tot_int : 0u) + *tot_split;  // new internal nodes
     out[2] = (unsigned long long)(I > 0 ? (uint64_t)I - *tot_int : 0u);  // merged nodes
     out[3] = st->k_eff;
-    out[4] = st->deepest;
+    out[4] = d;
 }
 
 // RAII list of temporaries from the tree's allocator
@@ -461,15 +506,15 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     uint32_t* cnt_le = tmp.get<uint32_t>(L);
     uint32_t* bsum = tmp.get<uint32_t>(scan_scratch_elems(std::max(L, I)));
     uint32_t* tots = tmp.get<uint32_t>(8);
+    constexpr int kDeepMax = 1024;
+    uint32_t* deep = tmp.get<uint32_t>(kDeepMax);
     unsigned long long* totals = tmp.get<unsigned long long>(5);
     if (!tmp.ok) return fail(DOT_ENOMEM, "dot_refine: scratch allocation failed");
 
     // 1. tree metadata, merge marks, candidate keys
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(L)), dim3(TPB), 0, s, reinterpret_cast<uint32_t*>(cover), L,
-                       0xffffffffu);
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(L)), dim3(TPB), 0, s, hist_first, L, 0u);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(TPB), 0, s, tots, (int64_t)8, 0u);
-    hipLaunchKernelGGL(k_unselected, dim3(blocks_for(L)), dim3(TPB), 0, s, signal, L, p.prune_tau, p.prune_le, unsel);
+    hipLaunchKernelGGL(k_leaf_init, dim3(blocks_for(L)), dim3(TPB), 0, s, signal, t.leaf_depth, L, p.prune_tau, p.prune_le,
+                       p.max_depth, unsel, keys, cover, hist_first);
     hipError_t e = scan_u32(unsel, pre_unsel, L, bsum, &tots[4], s);
     if (e != hipSuccess) return hip_fail(e, "dot_refine: scan");
     if (I > 0) {
@@ -482,21 +527,23 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
                            pre_unsel, rec, survive, root, need);
         hipLaunchKernelGGL(k_cover, dim3(blocks_for(I)), dim3(TPB), 0, s, I, root, first, last, cover);
     }
-    hipLaunchKernelGGL(k_keys, dim3(blocks_for(L)), dim3(TPB), 0, s, signal, t.leaf_depth, L, p.prune_tau,
-                       p.prune_le, p.max_depth, keys);
-    // 2. exact top-k by radix select over the 64-bit keys
-    hipLaunchKernelGGL(k_sel_init, dim3(1), dim3(256), 0, s, sel);
+    // 2. exact top-k by radix select over the 64-bit keys: three digits of the
+    // signal's 32 bits, three of the index
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(TPB), 0, s, reinterpret_cast<uint32_t*>(sel),
+                       (int64_t)(sizeof(SelState) / 4), 0u);
     if (k_req > 0) {
-        for (int pass = 0; pass < 8; ++pass) {
-            int shift = 56 - 8 * pass;
-            hipLaunchKernelGGL(k_hist, dim3(blocks_for(L, 8)), dim3(256), 0, s, keys, L, shift, sel);
-            hipLaunchKernelGGL(k_sel_digit, dim3(1), dim3(64), 0, s, sel, shift, pass == 0 ? 1 : 0,
-                               (long long)k_req);
+        const unsigned g = (unsigned)std::min<int64_t>(blocks_for(L, 16), 1024);
+        const int bits[6] = {11, 11, 10, 11, 11, 10};
+        for (int pass = 0, shift = 64; pass < 6; ++pass) {
+            shift -= bits[pass];
+            hipLaunchKernelGGL(k_select, dim3(g), dim3(TPB), 0, s, keys, L, shift, bits[pass], pass == 0 ? 1 : 0,
+                               (unsigned long long)k_req, sel);
         }
     }
     // 3. counts and scans
-    hipLaunchKernelGGL(k_leaf_counts, dim3(blocks_for(L, 8)), dim3(TPB), 0, s, L, cover, first, keys,
-                       t.leaf_depth, ndepth, sel, cnt, split);
+    const int n_deep = (int)std::min<int64_t>(blocks_for(L, 2), kDeepMax);
+    hipLaunchKernelGGL(k_leaf_counts, dim3(n_deep), dim3(TPB), 0, s, L, cover, first, keys, t.leaf_depth, ndepth, sel, cnt,
+                       split, deep);
     if (I > 0) hipLaunchKernelGGL(k_first_hist, dim3(blocks_for(I)), dim3(TPB), 0, s, I, survive, first, hist_first);
     e = scan_u32(cnt, nl, L, bsum, &tots[0], s);
     if (e == hipSuccess) e = scan_u32(split, rank_split, L, bsum, &tots[1], s);
@@ -505,7 +552,8 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     if (e != hipSuccess) return hip_fail(e, "dot_refine: scans");
     // cnt_le becomes inclusive: surviving nodes whose first leaf is <= l
     hipLaunchKernelGGL(k_add_u32, dim3(blocks_for(L)), dim3(TPB), 0, s, cnt_le, (const uint32_t*)hist_first, L);
-    hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, s, L, I, nl, cnt, &tots[3], &tots[1], sel, totals);
+    hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, s, L, I, nl, cnt, &tots[3], &tots[1], sel,
+                       deep, n_deep, totals);
     unsigned long long h_tot[5];
     e = hipMemcpyAsync(h_tot, totals, sizeof(h_tot), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -529,7 +577,7 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
         return fail(DOT_ENOMEM, "dot_refine: allocation of the refined planes failed");
     }
     if (I > 0)
-        hipLaunchKernelGGL(k_child_internal, dim3(blocks_for(I)), dim3(TPB), 0, s, t.child, I, survive, first,
+        hipLaunchKernelGGL(k_child_internal, dim3(blocks_for(I * 8)), dim3(TPB), 0, s, t.child, I, survive, first,
                            rank_int, rank_split, split, cnt_le, nl, child2);
     hipLaunchKernelGGL(k_child_split, dim3(blocks_for(L)), dim3(TPB), 0, s, L, split, rank_split, cnt_le, nl, child2);
     hipLaunchKernelGGL(k_sources, dim3(blocks_for(L)), dim3(TPB), 0, s, L, cover, first, split, nl, src);
