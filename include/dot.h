@@ -499,8 +499,8 @@ int dot_mse_grad(const float *pred, const float *target, const int64_t *target_i
  *  uint16 index of its box.  The tree becomes DOT_PAL16 in place (sigma
  *  rounded to FP16).  Rendering, serving, the signal calls and dot_export
  *  accept it; dot_render_backward, the optimiser steps and dot_refine return
- *  DOT_EUNSUPPORTED.  Needs scratch of about 2 N (3K + 4) * 4 bytes from the
- *  tree's allocator; synchronises `stream`.
+ *  DOT_EUNSUPPORTED.  Needs scratch of about 16 bytes per leaf from the tree's
+ *  allocator; synchronises `stream`.
  *  Errors: DOT_EINVAL on bits outside 1..16 or an already compressed tree;
  *  DOT_ENOMEM when the scratch cannot be allocated.
  */
