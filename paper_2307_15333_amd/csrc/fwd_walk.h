@@ -80,8 +80,11 @@ struct FwdWave {
     int fetched = 0;
     int64_t rid = 0;    // COUNT: the ray's index in the batch (record column)
     int nrec = 0;       // COUNT: composited segments recorded so far
-    int64_t pend_j = -1;
+    // COUNT: the last record's bucket slot is stored with the next record (or at
+    // the end of the ray), so the walk never waits for the atomic
     uint32_t pend_slot = 0;
+    uint32_t run_base = 0;    // COUNT: what the atomic of this lane's run returned (in its first lane)
+    int run_rank = -1;        // place in its run of this lane's record; -1: none pending
 
     // a segment's data in flight
     struct Fetch {
@@ -125,7 +128,40 @@ struct FwdWave {
 
     __device__ __forceinline__ void flush_slot() {
         if constexpr (COUNT)
-            if (pend_j >= 0) a.rec.slot[pend_j] = pend_slot;
+            if (nrec > 0) a.rec.slot[(int64_t)(min(nrec, a.rec.cap) - 1) * a.rec.n + rid] = pend_slot;
+    }
+
+    // the slot of the last step's record, from the first lane of its run; called
+    // by all lanes of the wave
+    __device__ __forceinline__ void resolve_slot() {
+        if constexpr (COUNT) {
+            const int head = (int)__lane_id() - run_rank;
+            const uint32_t base = (uint32_t)__builtin_amdgcn_ds_bpermute(head << 2, (int)run_base);
+            if (run_rank >= 0) pend_slot = base + (uint32_t)run_rank;
+            run_rank = -1;
+        }
+    }
+
+    // One counting atomic for each run of neighbouring lanes in the same leaf (the
+    // device completes 15 to 27 G counting atomics a second, which bounds a
+    // training forward; lanes next to each other are neighbouring pixels).
+    // key >= 0: a recorded segment of that leaf; < -1: another one of leaf
+    // -2 - key; -1: none.  Called by all lanes of the wave.
+    __device__ __forceinline__ void count_runs(int key) {
+        const int lane = (int)__lane_id();
+        const int prev = __builtin_amdgcn_update_dpp(~key, key, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+        const uint64_t heads = __ballot(key != prev);
+        const uint64_t le = 2ull * (1ull << lane) - 1ull;        // lanes up to this one
+        const int head = 63 - __builtin_clzll(heads & le);
+        const uint64_t above = heads & ~le;
+        const int end = above ? __builtin_ctzll(above) : WAVE;
+        if (head == lane && key != -1) {
+            if (key >= 0)
+                run_base = atomicAdd(&a.leaf_count[key], (uint32_t)(end - lane));
+            else
+                atomicAdd(&a.leaf_rest[-2 - key], (uint32_t)(end - lane));
+        }
+        if (key >= 0) run_rank = lane - head;
     }
 
     template <int R>
@@ -226,26 +262,21 @@ struct FwdWave {
     __device__ __forceinline__ bool shade(int leaf, float delta, bool in, const Fetch& f) {
         float x[3];
         if constexpr (QUAD && COLOUR) dots(f, x);
-        if (!in) return true;
-        const float sg = fmaxf(f.sg, 0.f);
-        const float tau = sg * delta;
-        ++n;
-        fetched += tau > 0.f;
-        [[maybe_unused]] uint32_t slot = 0;
         [[maybe_unused]] bool record = false;
         if constexpr (COUNT) {
             // a training forward counts, per leaf, the segments whose gradient rows
             // its adjoint emits; a segment it records also reserves its row's slot
             // in the leaf's bucket (issued here, early, and consumed one record later)
-            if (sg > 0.f) {
-                if (a.rec.a && nrec < a.rec.cap) {
-                    slot = atomicAdd(&a.leaf_count[leaf], 1u);
-                    record = true;
-                } else {
-                    atomicAdd(&a.leaf_rest[leaf], 1u);
-                }
-            }
+            resolve_slot();
+            const bool counted = in && f.sg > 0.f;
+            record = counted && a.rec.a && nrec < a.rec.cap;
+            count_runs(record ? leaf : counted ? -2 - leaf : -1);
         }
+        if (!in) return true;
+        const float sg = fmaxf(f.sg, 0.f);
+        const float tau = sg * delta;
+        ++n;
+        fetched += tau > 0.f;
         if constexpr (!QUAD && COLOUR) dots(f, x);
         const float Sn = S + tau;
         const float Tn = __expf(-Sn);
@@ -266,8 +297,6 @@ struct FwdWave {
                 a.rec.a[j] = make_float4(__int_as_float(leaf), delta, tau, cv[0]);
                 a.rec.b[j] = make_float2(cv[1], cv[2]);
                 flush_slot();
-                pend_j = j;
-                pend_slot = slot;
             }
             if (sg > 0.f && a.rec.a) ++nrec;
         }

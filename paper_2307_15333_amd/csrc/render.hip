@@ -35,6 +35,7 @@ __global__ __launch_bounds__(BLOCK, FAR ? 1 : MODE == 3 ? 6 : fwd_waves(DT, DEG)
             walk_fwd<true>(tv, r, live, &stack_lds[tid], seg, desc);
         else
             walk_fwd<false>(tv, r, live, &stack_lds[tid], seg, desc);
+        seg.resolve_slot();
         // the index again, rather than two registers held through the walk
         if (!ray_index(rb, tile, lane, rid)) return;
     }
