@@ -528,7 +528,7 @@ struct FwdSeg {
             // (stored with the next record) the reserved slot
             if constexpr (COUNT) {
                 if (record) {
-                    const int64_t j = (int64_t)nrec * a.rec.n + rid;
+                    const int64_t j = a.rec.at(nrec, rid);
                     a.rec.a[j] = make_float4(__int_as_float(leaf), delta, tau, cv[0]);
                     a.rec.b[j] = make_float2(cv[1], cv[2]);
                     flush_slot();

@@ -167,9 +167,11 @@ struct RayBatch {
 };
 
 // Segment records of a training forward, replayed by the adjoint instead of a
-// second traversal: per ray up to `cap` composited segments (sigma > 0), slot
-// major ([slot][ray]) so one step's writes and reads are coalesced, each with
-// the bucket slot the forward reserved for its gradient row.  A ray with more
+// second traversal: per ray up to `cap` composited segments (sigma > 0), each
+// with the bucket slot the forward reserved for its gradient row.  Records lie
+// in groups of four slots, [slot / 4][ray][slot % 4], so that what a ray writes
+// (and replays) together is together in memory and neighbouring rays' groups
+// are neighbours; a last group of cap % 4 slots follows.  A ray with more
 // segments is listed; the adjoint replays its first `cap` and re-traverses it
 // for the rest.  The buffer's size sets `cap`.
 //
@@ -179,15 +181,21 @@ struct RayBatch {
 // those, taken in the adjoint).  Bucket l holds [0][l] + [1][l] rows.
 constexpr int SEG_CAP_MAX = 1024;
 struct SegRecords {
-    float4* a = nullptr;          // [cap][n]: leaf id bits, delta, tau, c0
-    float2* b = nullptr;          // [cap][n]: c1, c2
-    uint32_t* slot = nullptr;     // [cap][n]: bucket slot of the record's row
+    float4* a = nullptr;          // [cap n]: leaf id bits, delta, tau, c0
+    float2* b = nullptr;          // [cap n]: c1, c2
+    uint32_t* slot = nullptr;     // [cap n]: bucket slot of the record's row
     int32_t* count = nullptr;     // [n]: records of the ray
     uint32_t* overflow = nullptr; // [1]: rays with more than `cap` records
     uint32_t* total = nullptr;    // [1]: segments with sigma > 0 of the batch (= bucket rows of its adjoint)
     int32_t* olist = nullptr;     // [n]: ids of those rays (first `overflow` entries)
     int64_t n = 0;                // rays the buffer holds (the slot stride)
     int cap = 0;                  // records per ray
+
+    // index of record s (< cap) of ray r
+    __device__ __forceinline__ int64_t at(int s, int64_t r) const {
+        const int g = s & ~3, w = min(cap - g, 4);
+        return (int64_t)g * n + r * w + (s - g);
+    }
 };
 size_t seg_records_bytes(int64_t n_rays, int cap);
 // view of a buffer of `bytes` for n rays; cap = 0 when it is too small for one record

@@ -57,6 +57,15 @@ __device__ __forceinline__ uint32_t times3(int x) {
     return r;
 }
 
+// Contributing segments of a training forward wait here for STAGE_STEPS steps of
+// the wave: [step][thread], leaf (or -2 - leaf beyond the record capacity, -1:
+// none), delta, tau and the colour.
+constexpr int STAGE_STEPS = 4;
+struct Stage {
+    float4 a[STAGE_STEPS][BLOCK];
+    float2 b[STAGE_STEPS][BLOCK];
+};
+
 // The ray's compositing state (see FwdSeg, which computes the same per lane).
 // COLOUR = false: the weights alone (the signal pass), which need no row: 16
 // views of 800x800 over 3.5M FP32 leaves 3.11 -> 1.43 ms.
@@ -80,11 +89,8 @@ struct FwdWave {
     int fetched = 0;
     int64_t rid = 0;    // COUNT: the ray's index in the batch (record column)
     int nrec = 0;       // COUNT: composited segments recorded so far
-    // COUNT: the last record's bucket slot is stored with the next record (or at
-    // the end of the ray), so the walk never waits for the atomic
-    uint32_t pend_slot = 0;
-    uint32_t run_base = 0;    // COUNT: what the atomic of this lane's run returned (in its first lane)
-    int run_rank = -1;        // place in its run of this lane's record; -1: none pending
+    Stage* stage = nullptr;   // COUNT
+    int staged = 0;           // COUNT: steps waiting in it (the same in all lanes)
 
     // a segment's data in flight
     struct Fetch {
@@ -126,28 +132,11 @@ struct FwdWave {
         }
     }
 
-    __device__ __forceinline__ void flush_slot() {
-        if constexpr (COUNT)
-            if (nrec > 0) a.rec.slot[(int64_t)(min(nrec, a.rec.cap) - 1) * a.rec.n + rid] = pend_slot;
-    }
-
-    // the slot of the last step's record, from the first lane of its run; called
-    // by all lanes of the wave
-    __device__ __forceinline__ void resolve_slot() {
-        if constexpr (COUNT) {
-            const int head = (int)__lane_id() - run_rank;
-            const uint32_t base = (uint32_t)__builtin_amdgcn_ds_bpermute(head << 2, (int)run_base);
-            if (run_rank >= 0) pend_slot = base + (uint32_t)run_rank;
-            run_rank = -1;
-        }
-    }
-
     // One counting atomic for each run of neighbouring lanes in the same leaf (the
-    // device completes 15 to 27 G counting atomics a second, which bounds a
-    // training forward; lanes next to each other are neighbouring pixels).
-    // key >= 0: a recorded segment of that leaf; < -1: another one of leaf
-    // -2 - key; -1: none.  Called by all lanes of the wave.
-    __device__ __forceinline__ void count_runs(int key) {
+    // device completes 15 to 27 G counting atomics a second; lanes next to each
+    // other are neighbouring pixels).  key as in Stage; returns the slot of this
+    // lane's segment relative to `base`, which the run's first lane holds.
+    __device__ __forceinline__ int count_run(int key, uint32_t& base) const {
         const int lane = (int)__lane_id();
         const int prev = __builtin_amdgcn_update_dpp(~key, key, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
         const uint64_t heads = __ballot(key != prev);
@@ -155,13 +144,58 @@ struct FwdWave {
         const int head = 63 - __builtin_clzll(heads & le);
         const uint64_t above = heads & ~le;
         const int end = above ? __builtin_ctzll(above) : WAVE;
+        base = 0;
         if (head == lane && key != -1) {
             if (key >= 0)
-                run_base = atomicAdd(&a.leaf_count[key], (uint32_t)(end - lane));
+                base = atomicAdd(&a.leaf_count[key], (uint32_t)(end - lane));
             else
                 atomicAdd(&a.leaf_rest[-2 - key], (uint32_t)(end - lane));
         }
-        if (key >= 0) run_rank = lane - head;
+        return lane - head;
+    }
+
+    // Count and record the staged steps: per leaf the segments whose gradient rows
+    // the adjoint emits, each recorded one with the slot of its row in the leaf's
+    // bucket.  A ray's records lie in groups of four, so writing several steps
+    // together fills a group's lines while the L2 still holds them, and the atomics
+    // of those steps are in flight together (forward of 2^20 cell-ordered rays of
+    // 3.5M leaves: 1468 us when every step writes and counts by itself, 1348 so).
+    // Called by all lanes of the wave.
+    __device__ __forceinline__ void flush() {
+        if constexpr (COUNT) {
+            if (staged == 0) return;
+            const int tid = threadIdx.x;
+            int key[STAGE_STEPS], rank[STAGE_STEPS], n_key = 0;
+            uint32_t base[STAGE_STEPS];
+#pragma unroll
+            for (int j = 0; j < STAGE_STEPS; ++j) {
+                key[j] = j < staged ? __float_as_int(stage->a[j][tid].x) : -1;
+                n_key += key[j] != -1;
+            }
+#pragma unroll
+            for (int j = 0; j < STAGE_STEPS; ++j) rank[j] = count_run(key[j], base[j]);
+            if (a.rec.a) {
+                int at = nrec - n_key;
+#pragma unroll
+                for (int j = 0; j < STAGE_STEPS; ++j) {
+                    if (key[j] >= 0) {
+                        const int64_t i = a.rec.at(at, rid);
+                        a.rec.a[i] = stage->a[j][tid];
+                        a.rec.b[i] = stage->b[j][tid];
+                    }
+                    at += key[j] != -1;
+                }
+                at = nrec - n_key;
+#pragma unroll
+                for (int j = 0; j < STAGE_STEPS; ++j) {
+                    const int head = (int)__lane_id() - rank[j];
+                    const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute(head << 2, (int)base[j]);
+                    if (key[j] >= 0) a.rec.slot[a.rec.at(at, rid)] = b + (uint32_t)rank[j];
+                    at += key[j] != -1;
+                }
+            }
+            staged = 0;
+        }
     }
 
     template <int R>
@@ -258,60 +292,50 @@ struct FwdWave {
         }
     }
 
-    // composite the segment (in: this lane has one); false when the ray stops
+    // composite the segment (in: this lane has one); false when the ray stops.
+    // Called by all lanes of the wave.
     __device__ __forceinline__ bool shade(int leaf, float delta, bool in, const Fetch& f) {
-        float x[3];
-        if constexpr (QUAD && COLOUR) dots(f, x);
-        [[maybe_unused]] bool record = false;
-        if constexpr (COUNT) {
-            // a training forward counts, per leaf, the segments whose gradient rows
-            // its adjoint emits; a segment it records also reserves its row's slot
-            // in the leaf's bucket (issued here, early, and consumed one record later)
-            resolve_slot();
-            const bool counted = in && f.sg > 0.f;
-            record = counted && a.rec.a && nrec < a.rec.cap;
-            count_runs(record ? leaf : counted ? -2 - leaf : -1);
-        }
-        if (!in) return true;
+        float x[3], cv[3] = {0.f, 0.f, 0.f};
+        if constexpr (COLOUR) dots(f, x);
         const float sg = fmaxf(f.sg, 0.f);
         const float tau = sg * delta;
-        ++n;
-        fetched += tau > 0.f;
-        if constexpr (!QUAD && COLOUR) dots(f, x);
-        const float Sn = S + tau;
-        const float Tn = __expf(-Sn);
-        const float w = fmaxf(T - Tn, 0.f);
-        float cv[3];
-        if constexpr (COLOUR) {
+        if (in) {
+            ++n;
+            fetched += tau > 0.f;
+            const float Sn = S + tau;
+            const float Tn = __expf(-Sn);
+            const float w = fmaxf(T - Tn, 0.f);
+            if constexpr (COLOUR) {
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                cv[ch] = sigmoidf_(x[ch]);
-                C[ch] = fmaf(w, cv[ch], C[ch]);
+                for (int ch = 0; ch < 3; ++ch) {
+                    cv[ch] = sigmoidf_(x[ch]);
+                    C[ch] = fmaf(w, cv[ch], C[ch]);
+                }
             }
+            if (a.signal) {
+                if (a.signal_mode == DOT_SIGNAL_MAX) {
+                    // non-negative floats order like their bit patterns; skip the
+                    // atomic when the stored value already dominates
+                    if (w > f.cur) atomicMax(reinterpret_cast<unsigned int*>(&a.signal[leaf]), __float_as_uint(w));
+                } else {
+                    unsafeAtomicAdd(&a.signal[leaf], w);
+                }
+            }
+            S = Sn;
+            T = Tn;
         }
         if constexpr (COUNT) {
-            // the record the adjoint replays: leaf, delta, tau, the colour and
-            // (stored with the next record) the reserved slot
-            if (record) {
-                const int64_t j = (int64_t)nrec * a.rec.n + rid;
-                a.rec.a[j] = make_float4(__int_as_float(leaf), delta, tau, cv[0]);
-                a.rec.b[j] = make_float2(cv[1], cv[2]);
-                flush_slot();
-            }
-            if (sg > 0.f && a.rec.a) ++nrec;
-        }
-        if (a.signal) {
-            if (a.signal_mode == DOT_SIGNAL_MAX) {
-                // non-negative floats order like their bit patterns; skip the
-                // atomic when the stored value already dominates
-                if (w > f.cur) atomicMax(reinterpret_cast<unsigned int*>(&a.signal[leaf]), __float_as_uint(w));
-            } else {
-                unsafeAtomicAdd(&a.signal[leaf], w);
+            const bool counted = in && sg > 0.f;
+            if (__any(counted)) {
+                const bool record = counted && a.rec.a && nrec < a.rec.cap;
+                const int key = record ? leaf : counted ? -2 - leaf : -1;
+                stage->a[staged][threadIdx.x] = make_float4(__int_as_float(key), delta, tau, cv[0]);
+                stage->b[staged][threadIdx.x] = make_float2(cv[1], cv[2]);
+                nrec += counted && a.rec.a;
+                if (++staged == STAGE_STEPS) flush();
             }
         }
-        S = Sn;
-        T = Tn;
-        return !(S > a.thr);
+        return !in || !(S > a.thr);
     }
 };
 
