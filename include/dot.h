@@ -418,7 +418,8 @@ int dot_sigma_signal(dot_tree_t tree, float *signal_out, void *stream);
  *  Writes the same rays as a DOT_RAYS_PIXELS list, cam_idx_out / pix_idx_out
  *  (DEVICE int32 [n]), grouped by screen tile -- square tiles sized to hold
  *  about 16 of the batch's rays, in camera-then-row-major tile order; order
- *  inside a tile unspecified -- so that a wave traces neighbouring pixels.
+ *  inside a tile unspecified (with a workspace of the size asked for below,
+ *  near pixels are kept together) -- so that a wave traces neighbouring pixels.
  *  ray_ids_out (DEVICE int64 [n] or NULL) receives the ids in the new order,
  *  for use as the target rows of dot_mse_loss.  The batch's content is
  *  unchanged (the loss is a mean and the gradient a sum over it).
@@ -446,8 +447,8 @@ int dot_pixel_batch(const int64_t *ray_ids, int64_t n_rays, int32_t width, int32
  *  from different threads) race and give wrong orders.
  *  Errors: as dot_pixel_batch, and DOT_EINVAL (before any device work) when
  *  the batch needs more than DOT_PIXEL_BATCH_SCRATCH_BYTES of scratch, i.e.
- *  when dot_pixel_batch_workspace(n, width, height, n_cams) exceeds it: about
- *  4 bytes per ray plus 8 per screen tile, so batches of up to 2^21 rays fit
+ *  when dot_pixel_batch_workspace(n, width, height, n_cams) exceeds it: at
+ *  least about 4 bytes per ray plus 8 per screen tile, so batches of up to 2^21 rays fit
  *  for any image set with fewer than 400,000 tiles, and about 3.5M rays of
  *  100 views at 800x800.
  */

@@ -718,10 +718,10 @@ int dot_pixel_batch(const int64_t* ray_ids, int64_t n_rays, int32_t width, int32
     if (n_rays == 0) return DOT_OK;
     if (!ray_ids || !cam_idx_out || !pix_idx_out || !workspace)
         return fail(DOT_EINVAL, "dot_pixel_batch: NULL ids, outputs or workspace");
-    if (workspace_bytes < pixel_batch_workspace_bytes(n_rays, width, height, n_cams))
+    if (workspace_bytes < pixel_batch_workspace_min(n_rays, width, height, n_cams))
         return fail(DOT_EINVAL, "dot_pixel_batch: workspace too small");
     hipError_t e = launch_pixel_batch(ray_ids, n_rays, width, height, n_cams, cam_idx_out, pix_idx_out, ray_ids_out,
-                                      workspace, static_cast<hipStream_t>(stream));
+                                      workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "dot_pixel_batch: launch");
     return DOT_OK;
 }
@@ -736,7 +736,7 @@ int dot_pixel_batch_noalloc(const int64_t* ray_ids, int64_t n_rays, int32_t widt
     if (n_rays > (int64_t)UINT32_MAX) return fail(DOT_EINVAL, "dot_pixel_batch_noalloc: more than 2^32 - 1 rays");
     if (n_rays == 0) return DOT_OK;
     if (!ray_ids || !cam_idx_out || !pix_idx_out) return fail(DOT_EINVAL, "dot_pixel_batch_noalloc: NULL ids or outputs");
-    const size_t need = pixel_batch_workspace_bytes(n_rays, width, height, n_cams);
+    const size_t need = pixel_batch_workspace_min(n_rays, width, height, n_cams);
     if (need > (size_t)DOT_PIXEL_BATCH_SCRATCH_BYTES)
         return fail(DOT_EINVAL, "dot_pixel_batch_noalloc: the batch needs " + std::to_string(need) +
                                     " bytes of scratch, more than the " +
@@ -745,7 +745,7 @@ int dot_pixel_batch_noalloc(const int64_t* ray_ids, int64_t n_rays, int32_t widt
     hipError_t e = pixel_batch_scratch(&ws);
     if (e != hipSuccess) return hip_fail(e, "dot_pixel_batch_noalloc: scratch address");
     e = launch_pixel_batch(ray_ids, n_rays, width, height, n_cams, cam_idx_out, pix_idx_out, ray_ids_out, ws,
-                           static_cast<hipStream_t>(stream));
+                           DOT_PIXEL_BATCH_SCRATCH_BYTES, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "dot_pixel_batch_noalloc: launch");
     return DOT_OK;
 }

@@ -294,9 +294,11 @@ hipError_t launch_rmsprop(const dot_tree& t, const float* gs, const float* gh, f
 hipError_t launch_sigma_signal(const dot_tree& t, float* out, hipStream_t s);
 hipError_t launch_mse(const float* pred, const float* target, const int64_t* idx, int64_t n, const double* gmul,
                       float* grad, double* loss, hipStream_t s);
+// bytes that a pixel batch takes, and the least it can do with (coarser order)
 size_t pixel_batch_workspace_bytes(int64_t n, int32_t W, int32_t H, int32_t n_cams);
+size_t pixel_batch_workspace_min(int64_t n, int32_t W, int32_t H, int32_t n_cams);
 hipError_t launch_pixel_batch(const int64_t* ids, int64_t n, int32_t W, int32_t H, int32_t n_cams, int32_t* cam_out,
-                              int32_t* pix_out, int64_t* id_out, void* ws, hipStream_t s);
+                              int32_t* pix_out, int64_t* id_out, void* ws, size_t ws_bytes, hipStream_t s);
 // device address of the no-allocation pixel batch's scratch on the current
 // device (DOT_PIXEL_BATCH_SCRATCH_BYTES)
 hipError_t pixel_batch_scratch(void** out);
