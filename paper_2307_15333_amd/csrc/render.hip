@@ -300,11 +300,12 @@ struct BwdCount {
     uint32_t* count;
     int n = 0, limit = 0;
     __device__ BwdCount(const TreeView& tv_, uint32_t* c) : tv(tv_), count(c) {}
-    __device__ __forceinline__ bool operator()(int leaf, float delta) {
+    __device__ __forceinline__ bool segment(int leaf, float sraw) {
         ++n;
-        if (load_sigma<DT>(tv.sigma, leaf) > 0.f) atomicAdd(&count[leaf], 1u);
+        if (sraw > 0.f) atomicAdd(&count[leaf], 1u);
         return n < limit;
     }
+    __device__ __forceinline__ bool operator()(int leaf, float) { return segment(leaf, load_sigma<DT>(tv.sigma, leaf)); }
 };
 
 // floats per bucket row: dsigma, a[3], then the direction when Y depends on it
@@ -339,89 +340,175 @@ struct BwdEmit {
                        float* r, uint32_t nr)
         : tv(tv_), offset(o), base0(b0), count(n_), cursor(c), rows(r), n_rows(nr) {}
 
-    __device__ __forceinline__ bool operator()(int leaf, float delta) {
+    __device__ __forceinline__ void begin(const Ray& r) { sh_basis<DEG>(d[0], d[1], d[2], Y); }
+
+    // x(ch): the SH sum of channel ch
+    template <class X>
+    __device__ __forceinline__ bool segment(int leaf, float delta, float sraw, X x) {
         ++n;
-        float sraw = load_sigma<DT>(tv.sigma, leaf);
-        if (sraw > 0.f && skip > 0) {
-            // a recorded segment: its row comes from the replay
-            --skip;
+        if (sraw > 0.f) {
             const float Sn = S + sraw * delta;
             const float Tn = __expf(-Sn);
             const float w = fmaxf(T - Tn, 0.f);
-            float row[3 * K];
-            load_sh_row<DT, 3 * K>(tv.sh, leaf, row);
+            float c[3], gs = 0.f;
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
-                P[ch] = fmaf(w, sigmoidf_(x), P[ch]);
-            }
-            S = Sn;
-            T = Tn;
-        } else if (sraw > 0.f) {
-            float tau = sraw * delta;
-            float Sn = S + tau;
-            float Tn = __expf(-Sn);
-            float w = fmaxf(T - Tn, 0.f);
-            float row[3 * K];
-            load_sh_row<DT, 3 * K>(tv.sh, leaf, row);
-            float c[3];
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                const float x = sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y);
-                c[ch] = sigmoidf_(x);
-            }
-            float out[RS];
-            float gs = 0.f;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
+                c[ch] = sigmoidf_(x(ch));
                 P[ch] = fmaf(w, c[ch], P[ch]);
                 gs = fmaf(g[ch], Tn * c[ch] - (C[ch] - P[ch]), gs);
             }
-            out[0] = gs * delta;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) out[1 + ch] = w > 0.f ? g[ch] * w * c[ch] * (1.f - c[ch]) : 0.f;
-            if constexpr (RS == 8) {
-                out[4] = d[0];
-                out[5] = d[1];
-                out[6] = d[2];
-                out[7] = 0.f;
-            }
-            // the region holds exactly the segments the counting found; a slot
-            // past it is never written (the reduction reads written rows only)
-            uint32_t k = atomicAdd(&cursor[leaf], 1u);
-            const uint64_t slot = (uint64_t)offset[leaf] + (base0 ? base0[leaf] : 0u) + k;
-            if (k < count[leaf] && slot < n_rows) {
-                float4* dst = reinterpret_cast<float4*>(rows + (int64_t)slot * RS);
-#pragma unroll
-                for (int j = 0; j < RS / 4; ++j)
-                    dst[j] = make_float4(out[4 * j], out[4 * j + 1], out[4 * j + 2], out[4 * j + 3]);
-            }
             S = Sn;
             T = Tn;
+            if (skip > 0) {
+                --skip;       // a recorded segment: its row comes from the replay
+            } else {
+                float out[RS];
+                out[0] = gs * delta;
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) out[1 + ch] = w > 0.f ? g[ch] * w * c[ch] * (1.f - c[ch]) : 0.f;
+                if constexpr (RS == 8) {
+                    out[4] = d[0];
+                    out[5] = d[1];
+                    out[6] = d[2];
+                    out[7] = 0.f;
+                }
+                // the region holds exactly the segments the counting found; a slot
+                // past it is never written (the reduction reads written rows only)
+                uint32_t k = atomicAdd(&cursor[leaf], 1u);
+                const uint64_t slot = (uint64_t)offset[leaf] + (base0 ? base0[leaf] : 0u) + k;
+                if (k < count[leaf] && slot < n_rows) {
+                    float4* dst = reinterpret_cast<float4*>(rows + (int64_t)slot * RS);
+#pragma unroll
+                    for (int j = 0; j < RS / 4; ++j)
+                        dst[j] = make_float4(out[4 * j], out[4 * j + 1], out[4 * j + 2], out[4 * j + 3]);
+                }
+            }
         }
         return n < limit;
+    }
+
+    __device__ __forceinline__ bool operator()(int leaf, float delta) {
+        const float sraw = load_sigma<DT>(tv.sigma, leaf);
+        float row[3 * K];
+        if (sraw > 0.f) load_sh_row<DT, 3 * K>(tv.sh, leaf, row);
+        return segment(leaf, delta, sraw, [&](int ch) { return sh_dot<DT, DEG>([&](int k) { return row[ch * K + k]; }, Y); });
+    }
+};
+
+// BwdEmit and BwdCount on the wave-wide walk (FwdWave fetches the leaves): the
+// chain leaf -> row -> next leaf bounds these kernels, and here the next leaf is
+// found while the row is in flight (the rays past their records among 100k
+// explicit rays of an FP32 tree of degree 3: 206 -> 116 us).
+template <int DT, int DEG>
+struct EmitWave : BwdEmit<DT, DEG> {
+    using Emit = BwdEmit<DT, DEG>;
+    using Base = FwdWave<DT, DEG>;
+    using Fetch = typename Base::Fetch;
+    Base leaf_data;
+
+    __device__ EmitWave(const TreeView& tv_, const FwdArgs& none, const uint32_t* o, const uint32_t* b0, const uint32_t* n_,
+                        uint32_t* c, float* r, uint32_t nr)
+        : Emit(tv_, o, b0, n_, c, r, nr), leaf_data(tv_, none) {}
+    __device__ __forceinline__ void begin(const Ray& r) { leaf_data.begin(r); }
+    __device__ __forceinline__ void fetch_signal(int, bool, Fetch& f) { f.cur = 0.f; }
+    __device__ __forceinline__ void fetch(int leaf, bool in, Fetch& f) { leaf_data.fetch(leaf, in, f); }
+    __device__ __forceinline__ bool shade(int leaf, float delta, bool in, const Fetch& f) {
+        float x[3];
+        leaf_data.dots(f, x);
+        return !in || Emit::segment(leaf, delta, f.sg, [&](int ch) { return x[ch]; });
     }
 };
 
 template <int DT>
+struct CountWave : BwdCount<DT> {
+    using Base = FwdWave<DT, 0, false, false>;
+    using Fetch = typename Base::Fetch;
+    Base leaf_data;
+
+    __device__ CountWave(const TreeView& tv_, const FwdArgs& none, uint32_t* c) : BwdCount<DT>(tv_, c), leaf_data(tv_, none) {}
+    __device__ __forceinline__ void fetch_signal(int, bool, Fetch& f) { f.cur = 0.f; }
+    __device__ __forceinline__ void fetch(int leaf, bool in, Fetch& f) { leaf_data.fetch(leaf, in, f); }
+    __device__ __forceinline__ bool shade(int leaf, float, bool in, const Fetch& f) {
+        return !in || BwdCount<DT>::segment(leaf, f.sg);
+    }
+};
+
+// Walk the ray with `seg`, lane by lane in a far tree; called by all lanes of the
+// wave (live: this one has a ray to walk).
+template <bool FAR, class Seg>
+__device__ __forceinline__ void walk_any(const TreeView& tv, const Ray& r, bool live, int* stk, Seg& seg) {
+    int desc = 0;
+    if constexpr (FAR) {
+        if (live) traverse(tv, r, stk, seg, desc);
+    } else if (tv.links) {
+        walk_fwd<true>(tv, r, live, stk, seg, desc);
+    } else {
+        walk_fwd<false>(tv, r, live, stk, seg, desc);
+    }
+}
+
+template <int DT, bool FAR>
 __global__ __launch_bounds__(BLOCK) void bwd_count_kernel(TreeView tv, RayBatch rb, BwdArgs a, uint32_t* count) {
     __shared__ int stack_lds[LAT * BLOCK];
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int64_t tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + (tid >> 6);
     if (tile >= rb.n_tiles) return;
-    Ray r;
+    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
     int64_t rid;
-    if (!make_ray(rb, tile, lane, r, rid)) return;
-    BwdCount<DT> seg(tv, count);
-    seg.limit = a.nseg[rid];
-    if (seg.limit <= 0) return;
-    if (a.grad_rgb[3 * rid] == 0.f && a.grad_rgb[3 * rid + 1] == 0.f && a.grad_rgb[3 * rid + 2] == 0.f) return;
-    int desc = 0;
-    traverse(tv, r, &stack_lds[tid], seg, desc);
+    bool live = make_ray(rb, tile, lane, r, rid);
+    int limit = 0;
+    if (live) {
+        limit = a.nseg[rid];
+        live = limit > 0 && !(a.grad_rgb[3 * rid] == 0.f && a.grad_rgb[3 * rid + 1] == 0.f && a.grad_rgb[3 * rid + 2] == 0.f);
+    }
+    const FwdArgs none{};
+    auto run = [&](auto& seg) {
+        seg.limit = limit;
+        walk_any<FAR>(tv, r, live, &stack_lds[tid], seg);
+    };
+    if constexpr (FAR) {
+        BwdCount<DT> seg(tv, count);
+        run(seg);
+    } else {
+        CountWave<DT> seg(tv, none, count);
+        run(seg);
+    }
 }
 
-template <int DT, int DEG>
+// Emit the rows of one ray's contributing segments past the first `skip`;
+// called by all lanes of the wave (live: this one has a ray).
+template <int DT, int DEG, bool FAR>
+__device__ __forceinline__ void emit_ray(const TreeView& tv, const BwdArgs& a, const Ray& r, bool live, int64_t rid, int skip,
+                                         const uint32_t* offset, const uint32_t* base0, const uint32_t* count,
+                                         uint32_t* cursor, float* rows, int* stk) {
+    const FwdArgs none{};
+    auto run = [&](auto& seg) {
+        seg.skip = skip;
+        seg.limit = live ? a.nseg[rid] : 0;
+        live = seg.limit > 0;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            seg.C[ch] = live ? a.rgb_fwd[3 * rid + ch] : 0.f;
+            seg.g[ch] = live ? a.grad_rgb[3 * rid + ch] : 0.f;
+        }
+        live = live && !(seg.g[0] == 0.f && seg.g[1] == 0.f && seg.g[2] == 0.f);
+        seg.d[0] = (float)r.dx;
+        seg.d[1] = (float)r.dy;
+        seg.d[2] = (float)r.dz;
+        seg.begin(r);
+        walk_any<FAR>(tv, r, live, stk, seg);
+    };
+    if constexpr (FAR) {
+        BwdEmit<DT, DEG> seg(tv, offset, base0, count, cursor, rows, a.n_rows);
+        run(seg);
+    } else {
+        EmitWave<DT, DEG> seg(tv, none, offset, base0, count, cursor, rows, a.n_rows);
+        run(seg);
+    }
+}
+
+template <int DT, int DEG, bool FAR>
 __global__ __launch_bounds__(BLOCK) void bwd_emit_kernel(TreeView tv, RayBatch rb, BwdArgs a, const uint32_t* offset,
                                                          const uint32_t* base0, const uint32_t* count, uint32_t* cursor,
                                                          float* rows) {
@@ -430,30 +517,16 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_kernel(TreeView tv, RayBatch r
     const int lane = tid & (WAVE - 1);
     const int64_t tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + (tid >> 6);
     if (tile >= rb.n_tiles) return;
-    Ray r;
-    int64_t rid;
-    if (!make_ray(rb, tile, lane, r, rid)) return;
-    BwdEmit<DT, DEG> seg(tv, offset, base0, count, cursor, rows, a.n_rows);
-    seg.limit = a.nseg[rid];
-    if (seg.limit <= 0) return;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        seg.C[ch] = a.rgb_fwd[3 * rid + ch];
-        seg.g[ch] = a.grad_rgb[3 * rid + ch];
-    }
-    if (seg.g[0] == 0.f && seg.g[1] == 0.f && seg.g[2] == 0.f) return;
-    seg.d[0] = (float)r.dx;
-    seg.d[1] = (float)r.dy;
-    seg.d[2] = (float)r.dz;
-    sh_basis<DEG>(seg.d[0], seg.d[1], seg.d[2], seg.Y);
-    int desc = 0;
-    traverse(tv, r, &stack_lds[tid], seg, desc);
+    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
+    int64_t rid = 0;
+    const bool live = make_ray(rb, tile, lane, r, rid);
+    emit_ray<DT, DEG, FAR>(tv, a, r, live, rid, 0, offset, base0, count, cursor, rows, &stack_lds[tid]);
 }
 
 // Re-traversal of the rays with more segments than the records hold (their
 // ids listed by the forward), one ray per lane: the recorded first `cap`
 // contributing segments only advance the prefix sums, the rest are emitted.
-template <int DT, int DEG>
+template <int DT, int DEG, bool FAR>
 __global__ __launch_bounds__(BLOCK) void bwd_emit_list_kernel(TreeView tv, RayBatch rb, BwdArgs a, const int32_t* list,
                                                               int64_t nlist, const uint32_t* offset,
                                                               const uint32_t* base0, const uint32_t* count,
@@ -461,26 +534,11 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_list_kernel(TreeView tv, RayBa
     __shared__ int stack_lds[LAT * BLOCK];
     const int tid = threadIdx.x;
     const int64_t i = (int64_t)blockIdx.x * BLOCK + tid;
-    if (i >= nlist) return;
-    const int64_t rid = list[i];
-    if (rid < 0 || rid >= rb.n_rays) return;
-    Ray r = ray_of(rb, rid);
-    BwdEmit<DT, DEG> seg(tv, offset, base0, count, cursor, rows, a.n_rows);
-    seg.limit = a.nseg[rid];
-    seg.skip = a.rec.cap;
-    if (seg.limit <= 0) return;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        seg.C[ch] = a.rgb_fwd[3 * rid + ch];
-        seg.g[ch] = a.grad_rgb[3 * rid + ch];
-    }
-    if (seg.g[0] == 0.f && seg.g[1] == 0.f && seg.g[2] == 0.f) return;
-    seg.d[0] = (float)r.dx;
-    seg.d[1] = (float)r.dy;
-    seg.d[2] = (float)r.dz;
-    sh_basis<DEG>(seg.d[0], seg.d[1], seg.d[2], seg.Y);
-    int desc = 0;
-    traverse(tv, r, &stack_lds[tid], seg, desc);
+    const int64_t rid = i < nlist ? list[i] : -1;
+    const bool live = rid >= 0 && rid < rb.n_rays;
+    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
+    if (live) r = ray_of(rb, rid);
+    emit_ray<DT, DEG, FAR>(tv, a, r, live, rid, a.rec.cap, offset, base0, count, cursor, rows, &stack_lds[tid]);
 }
 
 // Replay of the forward's segment records (of every ray, the first `cap` of
@@ -1168,15 +1226,45 @@ static hipError_t bwd_atomic(const dot_tree& t, const RayBatch& rb, const BwdArg
     }
 }
 
+template <int DT, bool FAR>
+static void launch_emit_as(int deg, const TreeView& tv, const RayBatch& rb, const BwdArgs& a, const uint32_t* off,
+                           const uint32_t* b0, const uint32_t* cnt, uint32_t* cur, float* rows, dim3 grid, hipStream_t s) {
+    switch (deg) {
+        case 0: hipLaunchKernelGGL((bwd_emit_kernel<DT, 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
+        case 1: hipLaunchKernelGGL((bwd_emit_kernel<DT, 1, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
+        case 2: hipLaunchKernelGGL((bwd_emit_kernel<DT, 2, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
+        default: hipLaunchKernelGGL((bwd_emit_kernel<DT, 3, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
+    }
+}
+
 template <int DT>
 static void launch_emit(int deg, const TreeView& tv, const RayBatch& rb, const BwdArgs& a, const uint32_t* off,
                         const uint32_t* b0, const uint32_t* cnt, uint32_t* cur, float* rows, dim3 grid, hipStream_t s) {
+    if (tv.near)
+        launch_emit_as<DT, false>(deg, tv, rb, a, off, b0, cnt, cur, rows, grid, s);
+    else
+        launch_emit_as<DT, true>(deg, tv, rb, a, off, b0, cnt, cur, rows, grid, s);
+}
+
+// the rays past the record capacity (only FP32 trees record)
+template <bool FAR>
+static void launch_emit_list(int deg, const TreeView& tv, const RayBatch& rb, const BwdArgs& a, int64_t n, const uint32_t* off,
+                             const uint32_t* b0, const uint32_t* cnt, uint32_t* cur, float* rows, hipStream_t s) {
+    const dim3 g((unsigned)((n + BLOCK - 1) / BLOCK)), b(BLOCK);
     switch (deg) {
-        case 0: hipLaunchKernelGGL((bwd_emit_kernel<DT, 0>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
-        case 1: hipLaunchKernelGGL((bwd_emit_kernel<DT, 1>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
-        case 2: hipLaunchKernelGGL((bwd_emit_kernel<DT, 2>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
-        default: hipLaunchKernelGGL((bwd_emit_kernel<DT, 3>), grid, dim3(BLOCK), 0, s, tv, rb, a, off, b0, cnt, cur, rows); break;
+        case 0: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 0, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
+        case 1: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 1, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
+        case 2: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 2, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
+        default: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 3, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
     }
+}
+
+template <int DT>
+static void launch_count(const TreeView& tv, const RayBatch& rb, const BwdArgs& a, uint32_t* count, dim3 grid, hipStream_t s) {
+    if (tv.near)
+        hipLaunchKernelGGL((bwd_count_kernel<DT, false>), grid, dim3(BLOCK), 0, s, tv, rb, a, count);
+    else
+        hipLaunchKernelGGL((bwd_count_kernel<DT, true>), grid, dim3(BLOCK), 0, s, tv, rb, a, count);
 }
 
 // c = a + b elementwise (a bucket's two regions) and z = 0 (the bucket
@@ -1357,9 +1445,9 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
         hipLaunchKernelGGL(fill_u32_kernel, dim3(fg), dim3(256), 0, s, cursor, L, nullptr, 1);
         hipLaunchKernelGGL(fill_u32_kernel, dim3(fg), dim3(256), 0, s, count_own, L, nullptr, 1);
         switch (t.storage) {
-            case DOT_F32: hipLaunchKernelGGL(bwd_count_kernel<DOT_F32>, grid, dim3(BLOCK), 0, s, tv, rb, a, count_own); break;
-            case DOT_F16: hipLaunchKernelGGL(bwd_count_kernel<DOT_F16>, grid, dim3(BLOCK), 0, s, tv, rb, a, count_own); break;
-            default: hipLaunchKernelGGL(bwd_count_kernel<DOT_BF16>, grid, dim3(BLOCK), 0, s, tv, rb, a, count_own); break;
+            case DOT_F32: launch_count<DOT_F32>(tv, rb, a, count_own, grid, s); break;
+            case DOT_F16: launch_count<DOT_F16>(tv, rb, a, count_own, grid, s); break;
+            default: launch_count<DOT_BF16>(tv, rb, a, count_own, grid, s); break;
         }
     }
     hipError_t e = hipSuccess;
@@ -1417,15 +1505,11 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
             default: hipLaunchKernelGGL(bwd_emit_rec_kernel<3>, grid, dim3(BLOCK), 0, s, rb, a, L, offset, m, rows); break;
         }
         if (overflow > 0) {
-            // only FP32 trees record (training storage)
             const int64_t no = std::min<int64_t>(overflow, rb.n_rays);
-            const dim3 lg((unsigned)((no + BLOCK - 1) / BLOCK));
-            switch (t.degree) {
-                case 0: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 0>), lg, dim3(BLOCK), 0, s, tv, rb, ae, a.rec.olist, no, offset, base0, count, cursor, rows); break;
-                case 1: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 1>), lg, dim3(BLOCK), 0, s, tv, rb, ae, a.rec.olist, no, offset, base0, count, cursor, rows); break;
-                case 2: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 2>), lg, dim3(BLOCK), 0, s, tv, rb, ae, a.rec.olist, no, offset, base0, count, cursor, rows); break;
-                default: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 3>), lg, dim3(BLOCK), 0, s, tv, rb, ae, a.rec.olist, no, offset, base0, count, cursor, rows); break;
-            }
+            if (tv.near)
+                launch_emit_list<false>(t.degree, tv, rb, ae, no, offset, base0, count, cursor, rows, s);
+            else
+                launch_emit_list<true>(t.degree, tv, rb, ae, no, offset, base0, count, cursor, rows, s);
         }
     } else {
         switch (t.storage) {
