@@ -740,46 +740,100 @@ __device__ __forceinline__ void bucket_sum_thread(const float4* __restrict__ p, 
     }
 }
 
+// x of the lane whose number differs in bit OFF
+template <int OFF>
+__device__ __forceinline__ float lane_xor(float x) {
+    const int v = __float_as_int(x);
+    if constexpr (OFF == 8) return __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x128 /* row_ror:8 */, 0xf, 0xf, true));
+    else if constexpr (OFF == 4) {
+        const int up = __builtin_amdgcn_update_dpp(0, v, 0x104 /* row_shl:4 */, 0xf, 0x5, false);
+        return __int_as_float(__builtin_amdgcn_update_dpp(up, v, 0x114 /* row_shr:4 */, 0xf, 0xa, false));
+    } else if constexpr (OFF == 2) return quad_f<QUAD_XOR2>(x);
+    else return quad_f<QUAD_XOR1>(x);
+}
+
+// Lanes without bit OFF: a summed over the pair of lanes that differ in it; lanes
+// with it: b summed likewise.
+template <int OFF>
+__device__ __forceinline__ float pair_sum(float a, float b) {
+    if constexpr (OFF >= 16) {
+        const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+        if constexpr (OFF == 32) {
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        } else {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+    } else {
+        const bool up = threadIdx.x & OFF;
+        return (up ? b : a) + lane_xor<OFF>(up ? a : b);
+    }
+}
+
+// The sums of N values over the wave, one in each lane: every step halves the
+// values that a lane still holds, so N values take N + 5 exchanges instead of the
+// 6 N of a butterfly that leaves all sums in all lanes (at degree 3 that was 294
+// of them for each leaf, and what the kernels waited for).  column: the value
+// whose sum this lane returns, or -1 (another lane has it too).
+template <int N, int OFF = WAVE / 2>
+__device__ __forceinline__ float wave_fold(float (&v)[N], int& column) {
+    constexpr int H = (N + 1) / 2;
+    float w[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) w[i] = pair_sum<OFF>(v[i], i + H < N ? v[i + H] : v[i]);
+    float sum;
+    if constexpr (OFF > 1)
+        sum = wave_fold<H, OFF / 2>(w, column);
+    else {
+        sum = w[0];
+        column = 0;
+    }
+    if (column >= 0 && (threadIdx.x & OFF)) column = column + H < N ? column + H : -1;
+    return sum;
+}
+
 // Sum of the m rows at p taken by a whole wave (called by all its lanes with
 // the same p and m): lanes stride over the rows (consecutive lanes read
-// consecutive rows), then a butterfly leaves the totals in every lane.
+// consecutive rows; up to U rows of a lane in flight).  Returns the sum of this
+// lane's column: an SH coefficient, or dsigma (column NV); -1: none.
 template <int DEG>
-__device__ __forceinline__ void bucket_sum_wave(const float4* __restrict__ p, uint32_t m, float& gs, float* acc) {
+__device__ __forceinline__ float bucket_sum_wave(const float4* __restrict__ p, uint32_t m, int& column) {
     constexpr int NV = 3 * (DEG + 1) * (DEG + 1);
     constexpr int Q = bwd_row_floats<DEG>() / 4;
     constexpr int U = 4;          // rows per lane whose loads are issued together
-    const int lane = threadIdx.x & (WAVE - 1);
-    gs = 0.f;
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+    float gs = 0.f, acc[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) acc[j] = 0.f;
-    uint32_t r = lane;
-    for (; r + (U - 1) * WAVE < m; r += U * WAVE) {
+    for (uint32_t r0 = 0; r0 < m; r0 += U * WAVE) {
         float4 h[U], q[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            h[u] = p[(int64_t)(r + u * WAVE) * Q];
-            q[u] = Q == 2 ? p[(int64_t)(r + u * WAVE) * Q + (Q - 1)] : h[u];
+            if (r0 + u * WAVE < m) {      // the same in all lanes; a lane past the end reads the last row
+                const uint32_t r = min(r0 + u * WAVE + lane, m - 1);
+                h[u] = p[(int64_t)r * Q];
+                q[u] = Q == 2 ? p[(int64_t)r * Q + (Q - 1)] : h[u];
+            }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) bucket_add_row<DEG>(h[u], q[u], gs, acc);
+        for (int u = 0; u < U; ++u)
+            if (r0 + u * WAVE + lane < m) bucket_add_row<DEG>(h[u], q[u], gs, acc);
     }
-    for (; r < m; r += WAVE) {
-        const float4 h = p[(int64_t)r * Q];
-        bucket_add_row<DEG>(h, Q == 2 ? p[(int64_t)r * Q + (Q - 1)] : h, gs, acc);
-    }
+    float all[NV + 1];
 #pragma unroll
-    for (int off = WAVE / 2; off > 0; off >>= 1) {
-        gs += __shfl_xor(gs, off, WAVE);
-#pragma unroll
-        for (int j = 0; j < NV; ++j) acc[j] += __shfl_xor(acc[j], off, WAVE);
-    }
+    for (int j = 0; j < NV; ++j) all[j] = acc[j];
+    all[NV] = gs;
+    return wave_fold<NV + 1>(all, column);
 }
 
 // Buckets of more rows than this are left out of the thread-per-leaf sums and
 // reduced a wave per leaf by bwd_heavy_kernel: a thread-per-leaf sum would keep
 // the block waiting on its longest bucket (a few leaves of a large batch
-// collect thousands of rows).
-constexpr uint32_t kLightRows = 64;
+// collect thousands of rows).  Thread sums + wave sums at a limit of 16, 32 and
+// 64 rows: dense gradients of 100k explicit rays 124, 117 and 128 us, RMSProp
+// step of 2^20 rays over 3.5M leaves 825, 828 and 827 us.
+constexpr uint32_t kLightRows = 32;
 
 // Rows of the bucket of leaf l (0 for l >= L) and, for a light bucket, its sums
 // (zero otherwise).
@@ -828,28 +882,47 @@ __device__ __forceinline__ void fused_update(float* theta, int64_t ti, float* m,
     v[si] = vv;
 }
 
-// A leaf's bucket totals (held by every lane of the wave) applied by the wave:
-// lane k owns SH column k and lane 0 sigma.  A fused optimiser step updates
-// the leaf; otherwise the sums are added to the gradient arrays when the
-// bucket has rows.
+// Leaf l's bucket summed and applied by the wave (called by all its lanes with
+// the same l and m).  A fused optimiser step updates the leaf, each lane its
+// column, whose state is requested before the rows; otherwise the sums are added
+// to the gradient arrays when the bucket has rows.
 template <int DEG, int OPT>
-__device__ __forceinline__ void wave_leaf_apply(int64_t l, uint32_t m, float gs, const float* acc,
-                                                float* __restrict__ gsig, float* __restrict__ gsh,
-                                                float* __restrict__ sigma, float* __restrict__ sh, int stride,
-                                                const FusedOpt& o) {
+__device__ __forceinline__ void wave_leaf(int64_t l, uint32_t m, const uint32_t* __restrict__ offset,
+                                          const float* __restrict__ rows, float* __restrict__ gsig,
+                                          float* __restrict__ gsh, float* __restrict__ sigma, float* __restrict__ sh,
+                                          int stride, const FusedOpt& o) {
     constexpr int NV = 3 * (DEG + 1) * (DEG + 1);
-    static_assert(NV <= WAVE, "one lane per column");
-    const int lane = threadIdx.x & (WAVE - 1);
-    float mine = 0.f;
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-        if (lane == j) mine = acc[j];
+    constexpr int RS = bwd_row_floats<DEG>();
+    static_assert(NV < WAVE, "one lane per column");
+    const float4* p = reinterpret_cast<const float4*>(rows + (int64_t)offset[l] * RS);
+    int column;
     if constexpr (OPT != OPT_NONE) {
-        if (lane < NV) fused_update<OPT>(sh, l * stride + lane, o.m_sh, o.v_sh, l * NV + lane, mine, o.lr_sh, o);
-        if (lane == 0) fused_update<OPT>(sigma, l, o.m_sigma, o.v_sigma, l, gs, o.lr_sigma, o);
+        // the columns of wave_fold, before its sums are there
+        float none[NV + 1] = {};
+        (void)wave_fold<NV + 1>(none, column);
+        const bool is_sigma = column == NV;
+        float* th = is_sigma ? sigma + l : sh + l * stride + column;
+        float* v = is_sigma ? o.v_sigma + l : o.v_sh + l * NV + column;
+        float* mo = is_sigma ? o.m_sigma + l : o.m_sh + l * NV + column;
+        float th_ = 0.f, v_ = 0.f, m_ = 0.f;
+        if (column >= 0) {
+            th_ = *th;
+            v_ = *v;
+            if constexpr (OPT == OPT_ADAM) m_ = *mo;
+        }
+        const float g = bucket_sum_wave<DEG>(p, m, column);
+        if (column >= 0) {
+            opt_apply<OPT>(th_, m_, v_, g, is_sigma ? o.lr_sigma : o.lr_sh, o);
+            if constexpr (OPT == OPT_ADAM) *mo = m_;
+            *th = th_;
+            *v = v_;
+        }
     } else if (m > 0) {
-        if (lane < NV && mine != 0.f) gsh[l * NV + lane] += mine;
-        if (lane == 0) gsig[l] += gs;
+        const float g = bucket_sum_wave<DEG>(p, m, column);
+        if (column == NV)
+            gsig[l] += g;
+        else if (column >= 0 && g != 0.f)
+            gsh[l * NV + column] += g;
     }
 }
 
@@ -861,8 +934,6 @@ __device__ __forceinline__ void wave_heavy_leaves(int64_t l, uint32_t m, const u
                                                   const float* __restrict__ rows, float* __restrict__ gsig,
                                                   float* __restrict__ gsh, float* __restrict__ sigma,
                                                   float* __restrict__ sh, int stride, const FusedOpt& o) {
-    constexpr int NV = 3 * (DEG + 1) * (DEG + 1);
-    constexpr int RS = bwd_row_floats<DEG>();
     uint64_t heavy = __ballot(m > kLightRows);
     while (heavy) {
         const int j = __ffsll((unsigned long long)heavy) - 1;
@@ -871,9 +942,7 @@ __device__ __forceinline__ void wave_heavy_leaves(int64_t l, uint32_t m, const u
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)l >> 32), j);
         const int64_t lj = (int64_t)(((uint64_t)hi << 32) | lo);
         const uint32_t mj = (uint32_t)__builtin_amdgcn_readlane((int)m, j);
-        float gs, acc[NV];
-        bucket_sum_wave<DEG>(reinterpret_cast<const float4*>(rows + (int64_t)offset[lj] * RS), mj, gs, acc);
-        wave_leaf_apply<DEG, OPT>(lj, mj, gs, acc, gsig, gsh, sigma, sh, stride, o);
+        wave_leaf<DEG, OPT>(lj, mj, offset, rows, gsig, gsh, sigma, sh, stride, o);
     }
 }
 
@@ -1033,21 +1102,20 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_wave_kernel(
     const uint32_t* __restrict__ count, const uint32_t* __restrict__ cursor, const float* __restrict__ rows,
     float* __restrict__ gsig, float* __restrict__ gsh, float* __restrict__ sigma, float* __restrict__ sh, int stride,
     FusedOpt o) {
-    constexpr int NV = 3 * (DEG + 1) * (DEG + 1);
-    constexpr int RS = bwd_row_floats<DEG>();
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
     for (int64_t l = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; l < L; l += nw) {
         const uint32_t m = bucket_rows(l, base0, count, cursor);
-        float gs, acc[NV];
-        bucket_sum_wave<DEG>(reinterpret_cast<const float4*>(rows + (int64_t)offset[l] * RS), m, gs, acc);
-        wave_leaf_apply<DEG, OPT>(l, m, gs, acc, gsig, gsh, sigma, sh, stride, o);
+        wave_leaf<DEG, OPT>(l, m, offset, rows, gsig, gsh, sigma, sh, stride, o);
     }
 }
 
 // The heavy buckets the block reductions leave out: wave w of nw takes the
 // leaves w + nw i, 64 at a time (lane j: i = b + j), so a run of adjacent
 // heavy leaves (neighbours in space collect rows together) spreads over
-// neighbouring waves instead of queueing in one.
+// neighbouring waves instead of queueing in one.  Neighbouring waves sit on one
+// XCD, so that a line of the counts is read into one L2 and not into four.
+// Degree 3, buckets over 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
+// -> 33 us with the mapping; 2^20 rays over 3.5M leaves 200 -> 188 -> 167 us.
 template <int DEG, int OPT>
 __global__ __launch_bounds__(RED_BLOCK) void bwd_heavy_kernel(
     int64_t L, const uint32_t* __restrict__ offset, const uint32_t* __restrict__ base0,
@@ -1056,7 +1124,7 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_heavy_kernel(
     FusedOpt o) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+    const int64_t w = (xcd_block(blockIdx.x, gridDim.x) * RED_BLOCK + threadIdx.x) / WAVE;
     for (int64_t b = 0; w + nw * b < L; b += WAVE) {
         const int64_t l = w + nw * (b + lane);
         const uint32_t m = l < L ? bucket_rows(l, base0, count, cursor) : 0u;
