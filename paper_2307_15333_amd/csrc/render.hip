@@ -398,7 +398,7 @@ struct BwdEmit {
 // BwdEmit and BwdCount on the wave-wide walk (FwdWave fetches the leaves): the
 // chain leaf -> row -> next leaf bounds these kernels, and here the next leaf is
 // found while the row is in flight (the rays past their records among 100k
-// explicit rays of an FP32 tree of degree 3: 206 -> 116 us).
+// explicit rays of an FP32 tree of degree 3, alone: 206 -> 116 us).
 template <int DT, int DEG>
 struct EmitWave : BwdEmit<DT, DEG> {
     using Emit = BwdEmit<DT, DEG>;
@@ -523,24 +523,6 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_kernel(TreeView tv, RayBatch r
     emit_ray<DT, DEG, FAR>(tv, a, r, live, rid, 0, offset, base0, count, cursor, rows, &stack_lds[tid]);
 }
 
-// Re-traversal of the rays with more segments than the records hold (their
-// ids listed by the forward), one ray per lane: the recorded first `cap`
-// contributing segments only advance the prefix sums, the rest are emitted.
-template <int DT, int DEG, bool FAR>
-__global__ __launch_bounds__(BLOCK) void bwd_emit_list_kernel(TreeView tv, RayBatch rb, BwdArgs a, const int32_t* list,
-                                                              int64_t nlist, const uint32_t* offset,
-                                                              const uint32_t* base0, const uint32_t* count,
-                                                              uint32_t* cursor, float* rows) {
-    __shared__ int stack_lds[LAT * BLOCK];
-    const int tid = threadIdx.x;
-    const int64_t i = (int64_t)blockIdx.x * BLOCK + tid;
-    const int64_t rid = i < nlist ? list[i] : -1;
-    const bool live = rid >= 0 && rid < rb.n_rays;
-    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
-    if (live) r = ray_of(rb, rid);
-    emit_ray<DT, DEG, FAR>(tv, a, r, live, rid, a.rec.cap, offset, base0, count, cursor, rows, &stack_lds[tid]);
-}
-
 // Replay of the forward's segment records (of every ray, the first `cap` of
 // a ray with more): the same per-segment arithmetic as BwdEmit, without the
 // traversal and the leaf fetches, each row stored at the slot the forward
@@ -548,12 +530,13 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_list_kernel(TreeView tv, RayBa
 // the recorded region of a bucket has no cursor.  Same ray-to-lane mapping as
 // the traversal kernels.
 template <int DEG>
-__global__ __launch_bounds__(BLOCK) void bwd_emit_rec_kernel(RayBatch rb, BwdArgs a, int64_t L, const uint32_t* offset,
-                                                             uint32_t n_rows, float* rows) {
+__device__ __forceinline__ void replay_rays(const RayBatch& rb, const BwdArgs& a, int64_t L, const uint32_t* offset,
+                                            float* rows, int64_t block, int64_t n_blocks) {
     constexpr int RS = bwd_row_floats<DEG>();
+    const uint32_t n_rows = a.n_rows;
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x) * WAVES_PER_BLOCK + (tid >> 6);
+    const int64_t tile = xcd_block(block, n_blocks) * WAVES_PER_BLOCK + (tid >> 6);
     if (tile >= rb.n_tiles) return;
     Ray r;
     int64_t rid;
@@ -653,6 +636,37 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_rec_kernel(RayBatch rb, BwdArg
             T = Tn;
         }
     }
+}
+
+template <int DEG>
+__global__ __launch_bounds__(BLOCK) void bwd_emit_rec_kernel(RayBatch rb, BwdArgs a, int64_t L, const uint32_t* offset,
+                                                             float* rows) {
+    replay_rays<DEG>(rb, a, L, offset, rows, blockIdx.x, gridDim.x);
+}
+
+// The replay, and in the first list_blocks workgroups the re-traversal of the
+// rays with more segments than the records hold (their ids listed by the
+// forward), one ray per lane: the recorded first `cap` contributing segments only
+// advance the prefix sums, the rest are emitted.  These rays are few and long, a
+// launch of their own left most of the chip idle while they walked (100k explicit
+// rays, degree 3: 139 + 116 us in two launches, 180 us in one).
+template <int DEG, bool FAR>
+__global__ __launch_bounds__(BLOCK) void bwd_emit_rest_kernel(TreeView tv, RayBatch rb, BwdArgs a, int64_t nlist,
+                                                              unsigned list_blocks, const uint32_t* offset,
+                                                              const uint32_t* base0, const uint32_t* count,
+                                                              uint32_t* cursor, float* rows) {
+    __shared__ int stack_lds[LAT * BLOCK];
+    if (blockIdx.x >= list_blocks) {
+        replay_rays<DEG>(rb, a, tv.n_leaves, offset, rows, blockIdx.x - list_blocks, gridDim.x - list_blocks);
+        return;
+    }
+    const int tid = threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * BLOCK + tid;
+    const int64_t rid = i < nlist ? a.rec.olist[i] : -1;
+    const bool live = rid >= 0 && rid < rb.n_rays;
+    Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
+    if (live) r = ray_of(rb, rid);
+    emit_ray<DOT_F32, DEG, FAR>(tv, a, r, live, rid, a.rec.cap, offset, base0, count, cursor, rows, &stack_lds[tid]);
 }
 
 static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1314,17 +1328,20 @@ static void launch_emit(int deg, const TreeView& tv, const RayBatch& rb, const B
         launch_emit_as<DT, true>(deg, tv, rb, a, off, b0, cnt, cur, rows, grid, s);
 }
 
-// the rays past the record capacity (only FP32 trees record)
-template <bool FAR>
-static void launch_emit_list(int deg, const TreeView& tv, const RayBatch& rb, const BwdArgs& a, int64_t n, const uint32_t* off,
-                             const uint32_t* b0, const uint32_t* cnt, uint32_t* cur, float* rows, hipStream_t s) {
-    const dim3 g((unsigned)((n + BLOCK - 1) / BLOCK)), b(BLOCK);
-    switch (deg) {
-        case 0: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 0, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
-        case 1: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 1, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
-        case 2: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 2, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
-        default: hipLaunchKernelGGL((bwd_emit_list_kernel<DOT_F32, 3, FAR>), g, b, 0, s, tv, rb, a, a.rec.olist, n, off, b0, cnt, cur, rows); break;
+// The records replayed (only FP32 trees record), with the n rays past their capacity.
+template <int DEG>
+static void launch_replay(const TreeView& tv, const RayBatch& rb, const BwdArgs& a, int64_t n, const uint32_t* off,
+                          const uint32_t* b0, const uint32_t* cnt, uint32_t* cur, float* rows, dim3 grid, hipStream_t s) {
+    if (n == 0) {
+        hipLaunchKernelGGL(bwd_emit_rec_kernel<DEG>, grid, dim3(BLOCK), 0, s, rb, a, tv.n_leaves, off, rows);
+        return;
     }
+    const unsigned lb = (unsigned)((n + BLOCK - 1) / BLOCK + 7) & ~7u;      // whole rounds over the XCDs
+    const dim3 g(grid.x + lb);
+    if (tv.near)
+        hipLaunchKernelGGL((bwd_emit_rest_kernel<DEG, false>), g, dim3(BLOCK), 0, s, tv, rb, a, n, lb, off, b0, cnt, cur, rows);
+    else
+        hipLaunchKernelGGL((bwd_emit_rest_kernel<DEG, true>), g, dim3(BLOCK), 0, s, tv, rb, a, n, lb, off, b0, cnt, cur, rows);
 }
 
 template <int DT>
@@ -1566,18 +1583,12 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
     ae.n_rows = m;
     if (a.rec.a) {
         // replay the recorded segments; re-traverse only the rays with more
+        const int64_t no = std::min<int64_t>(overflow, rb.n_rays);
         switch (t.degree) {
-            case 0: hipLaunchKernelGGL(bwd_emit_rec_kernel<0>, grid, dim3(BLOCK), 0, s, rb, a, L, offset, m, rows); break;
-            case 1: hipLaunchKernelGGL(bwd_emit_rec_kernel<1>, grid, dim3(BLOCK), 0, s, rb, a, L, offset, m, rows); break;
-            case 2: hipLaunchKernelGGL(bwd_emit_rec_kernel<2>, grid, dim3(BLOCK), 0, s, rb, a, L, offset, m, rows); break;
-            default: hipLaunchKernelGGL(bwd_emit_rec_kernel<3>, grid, dim3(BLOCK), 0, s, rb, a, L, offset, m, rows); break;
-        }
-        if (overflow > 0) {
-            const int64_t no = std::min<int64_t>(overflow, rb.n_rays);
-            if (tv.near)
-                launch_emit_list<false>(t.degree, tv, rb, ae, no, offset, base0, count, cursor, rows, s);
-            else
-                launch_emit_list<true>(t.degree, tv, rb, ae, no, offset, base0, count, cursor, rows, s);
+            case 0: launch_replay<0>(tv, rb, ae, no, offset, base0, count, cursor, rows, grid, s); break;
+            case 1: launch_replay<1>(tv, rb, ae, no, offset, base0, count, cursor, rows, grid, s); break;
+            case 2: launch_replay<2>(tv, rb, ae, no, offset, base0, count, cursor, rows, grid, s); break;
+            default: launch_replay<3>(tv, rb, ae, no, offset, base0, count, cursor, rows, grid, s); break;
         }
     } else {
         switch (t.storage) {
