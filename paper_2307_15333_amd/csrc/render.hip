@@ -842,7 +842,7 @@ __device__ __forceinline__ float bucket_sum_wave(const float4* __restrict__ p, u
 }
 
 // Buckets of more rows than this are left out of the thread-per-leaf sums and
-// reduced a wave per leaf by bwd_heavy_kernel: a thread-per-leaf sum would keep
+// reduced a wave per leaf by heavy_leaves: a thread-per-leaf sum would keep
 // the block waiting on its longest bucket (a few leaves of a large batch
 // collect thousands of rows).  Thread sums + wave sums at a limit of 16, 32 and
 // 64 rows: dense gradients of 100k explicit rays 124, 117 and 128 us, RMSProp
@@ -967,8 +967,33 @@ __device__ __forceinline__ void wave_heavy_leaves(int64_t l, uint32_t m, const u
 // channel's columns of the block's leaves, so loads and stores are coalesced
 // in K-float runs (a thread-per-leaf row of 3K floats would touch a new cache
 // line per lane and instruction).  Heavy buckets are left out of that pass
-// (their leaves are neither read nor written) for bwd_heavy_kernel.
+// (their leaves are neither read nor written) for heavy_leaves.
 constexpr int RED_BLOCK = 256;
+
+// The heavy buckets the block reductions leave out: wave w of nw takes the
+// leaves w + nw i, 64 at a time (lane j: i = b + j), so a run of adjacent
+// heavy leaves (neighbours in space collect rows together) spreads over
+// neighbouring waves instead of queueing in one.  Neighbouring waves sit on one
+// XCD, so that a line of the counts is read into one L2 and not into four.
+// Degree 3, buckets over 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
+// -> 33 us with the mapping; 2^20 rays over 3.5M leaves 200 -> 188 -> 167 us.
+// The first workgroups of a block reduction do this, beside its own rather than
+// in a launch behind it: 74 + 42 -> 82 us and 650 + 180 -> 756 us.
+template <int DEG, int OPT>
+__device__ __forceinline__ void heavy_leaves(int64_t block, int64_t n_blocks, int64_t L, const uint32_t* __restrict__ offset,
+                                             const uint32_t* __restrict__ base0, const uint32_t* __restrict__ count,
+                                             const uint32_t* __restrict__ cursor, const float* __restrict__ rows,
+                                             float* __restrict__ gsig, float* __restrict__ gsh, float* __restrict__ sigma,
+                                             float* __restrict__ sh, int stride, const FusedOpt& o) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t nw = n_blocks * RED_BLOCK / WAVE;
+    const int64_t w = (xcd_block(block, n_blocks) * RED_BLOCK + threadIdx.x) / WAVE;
+    for (int64_t b = 0; w + nw * b < L; b += WAVE) {
+        const int64_t l = w + nw * (b + lane);
+        const uint32_t m = l < L ? bucket_rows(l, base0, count, cursor) : 0u;
+        wave_heavy_leaves<DEG, OPT>(l, m, offset, rows, gsig, gsh, sigma, sh, stride, o);
+    }
+}
 
 template <int DEG>
 __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const uint32_t* __restrict__ offset,
@@ -976,12 +1001,18 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const 
                                                                const uint32_t* __restrict__ count,
                                                                const uint32_t* __restrict__ cursor,
                                                                const float* __restrict__ rows,
-                                                               float* __restrict__ gsig, float* __restrict__ gsh) {
+                                                               float* __restrict__ gsig, float* __restrict__ gsh,
+                                                               unsigned heavy_blocks) {
     constexpr int K = (DEG + 1) * (DEG + 1);
     constexpr int NV = 3 * K;
     constexpr int KP = K + 1;
     __shared__ float stage[RED_BLOCK * KP];
-    const int64_t l0 = (int64_t)blockIdx.x * RED_BLOCK;
+    if (blockIdx.x < heavy_blocks) {
+        heavy_leaves<DEG, OPT_NONE>(blockIdx.x, heavy_blocks, L, offset, base0, count, cursor, rows, gsig, gsh, nullptr,
+                                    nullptr, 0, FusedOpt{});
+        return;
+    }
+    const int64_t l0 = (int64_t)(blockIdx.x - heavy_blocks) * RED_BLOCK;
     const int64_t l = l0 + threadIdx.x;
     float gs, acc[NV];
     const uint32_t m = bucket_sum_light<DEG>(l, L, offset, base0, count, cursor, rows, gs, acc);
@@ -1009,7 +1040,7 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const 
 // RMSProp then leaves its values exactly as they are (lr 0 / (sqrt(v) + eps)
 // = 0) and only decays the square average, so the values are neither read
 // nor written; Adam still moves such a leaf by its first moment.  hit[r] = 2
-// marks a heavy bucket, whose leaf bwd_heavy_kernel updates.
+// marks a heavy bucket, whose leaf heavy_leaves updates.
 template <int K, int NV, int W, int OPT>
 __device__ __forceinline__ void fused_channel(int64_t l0, int nl, int ch, const float* stage, const int* hit,
                                               float* __restrict__ sh, int stride, const FusedOpt& o) {
@@ -1077,7 +1108,7 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_fused_kernel(int64_t L, const u
                                                               const uint32_t* __restrict__ cursor,
                                                               const float* __restrict__ rows,
                                                               float* __restrict__ sigma, float* __restrict__ sh,
-                                                              int stride, FusedOpt o) {
+                                                              int stride, FusedOpt o, unsigned heavy_blocks) {
     constexpr int NV = 3 * (DEG + 1) * (DEG + 1);
     // the sums of all 3K columns staged at once, so every row of the state is
     // swept in one pass (per channel, the half-lines a row shares with the
@@ -1085,7 +1116,12 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_fused_kernel(int64_t L, const u
     constexpr int KC = NV, KP = KC + 1;
     __shared__ float stage[RED_BLOCK * KP];
     __shared__ int hit[RED_BLOCK];
-    const int64_t l0 = (int64_t)blockIdx.x * RED_BLOCK;
+    if (blockIdx.x < heavy_blocks) {
+        heavy_leaves<DEG, OPT>(blockIdx.x, heavy_blocks, L, offset, base0, count, cursor, rows, nullptr, nullptr, sigma,
+                               sh, stride, o);
+        return;
+    }
+    const int64_t l0 = (int64_t)(blockIdx.x - heavy_blocks) * RED_BLOCK;
     const int64_t l = l0 + threadIdx.x;
     float gs, acc[NV];
     const uint32_t m = bucket_sum_light<DEG>(l, L, offset, base0, count, cursor, rows, gs, acc);
@@ -1093,7 +1129,7 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_fused_kernel(int64_t L, const u
     if (l < L) {
         hit[threadIdx.x] = heavy ? 2 : (m > 0 ? 1 : 0);
         if (heavy) {
-            // left to bwd_heavy_kernel
+            // left to heavy_leaves
         } else if (OPT == OPT_RMSPROP && m == 0) {
             float th = 0.f, mm = 0.f;         // g = 0: sigma stays, its square average decays
             opt_apply<OPT>(th, mm, o.v_sigma[l], 0.f, o.lr_sigma, o);
@@ -1123,29 +1159,6 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_wave_kernel(
     }
 }
 
-// The heavy buckets the block reductions leave out: wave w of nw takes the
-// leaves w + nw i, 64 at a time (lane j: i = b + j), so a run of adjacent
-// heavy leaves (neighbours in space collect rows together) spreads over
-// neighbouring waves instead of queueing in one.  Neighbouring waves sit on one
-// XCD, so that a line of the counts is read into one L2 and not into four.
-// Degree 3, buckets over 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
-// -> 33 us with the mapping; 2^20 rays over 3.5M leaves 200 -> 188 -> 167 us.
-template <int DEG, int OPT>
-__global__ __launch_bounds__(RED_BLOCK) void bwd_heavy_kernel(
-    int64_t L, const uint32_t* __restrict__ offset, const uint32_t* __restrict__ base0,
-    const uint32_t* __restrict__ count, const uint32_t* __restrict__ cursor, const float* __restrict__ rows,
-    float* __restrict__ gsig, float* __restrict__ gsh, float* __restrict__ sigma, float* __restrict__ sh, int stride,
-    FusedOpt o) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-    const int64_t w = (xcd_block(blockIdx.x, gridDim.x) * RED_BLOCK + threadIdx.x) / WAVE;
-    for (int64_t b = 0; w + nw * b < L; b += WAVE) {
-        const int64_t l = w + nw * (b + lane);
-        const uint32_t m = l < L ? bucket_rows(l, base0, count, cursor) : 0u;
-        wave_heavy_leaves<DEG, OPT>(l, m, offset, rows, gsig, gsh, sigma, sh, stride, o);
-    }
-}
-
 static FusedOpt fused_opt(const BwdArgs& a) {
     FusedOpt o{};
     o.m_sigma = a.m_sigma;
@@ -1170,36 +1183,34 @@ static FusedOpt fused_opt(const BwdArgs& a) {
 
 static int opt_kind(const BwdArgs& a) { return a.adam ? OPT_ADAM : a.rms ? OPT_RMSPROP : OPT_NONE; }
 
-// HEAVY: bwd_heavy_kernel (the buckets a block reduction left out), else
-// bwd_reduce_wave_kernel (every leaf)
-template <int DEG, int OPT, bool HEAVY>
+// every leaf by a wave
+template <int DEG, int OPT>
 static void launch_wave_opt(const dot_tree& t, const BwdArgs& a, const uint32_t* offset, const uint32_t* base0,
                             const uint32_t* count, const uint32_t* cursor, const float* rows, hipStream_t s) {
     const int64_t L = t.n_leaves;
-    const int64_t want = HEAVY ? (L + RED_BLOCK - 1) / RED_BLOCK : (L + RED_BLOCK / WAVE - 1) / (RED_BLOCK / WAVE);
-    const unsigned g = (unsigned)std::min<int64_t>(want, HEAVY ? 2048 : 1 << 16);
+    const int64_t want = (L + RED_BLOCK / WAVE - 1) / (RED_BLOCK / WAVE);
+    const unsigned g = (unsigned)std::min<int64_t>(want, 1 << 16);
     float* gsig = OPT == OPT_NONE ? a.grad_sigma : nullptr;
     float* gsh = OPT == OPT_NONE ? a.grad_sh : nullptr;
     float* sg = OPT == OPT_NONE ? nullptr : static_cast<float*>(t.sigma);
     float* sh = OPT == OPT_NONE ? nullptr : static_cast<float*>(t.sh);
     const FusedOpt o = OPT == OPT_NONE ? FusedOpt{} : fused_opt(a);
-    if constexpr (HEAVY)
-        hipLaunchKernelGGL((bwd_heavy_kernel<DEG, OPT>), dim3(g), dim3(RED_BLOCK), 0, s, L, offset, base0, count,
-                           cursor, rows, gsig, gsh, sg, sh, t.sh_stride, o);
-    else
-        hipLaunchKernelGGL((bwd_reduce_wave_kernel<DEG, OPT>), dim3(g), dim3(RED_BLOCK), 0, s, L, offset, base0,
-                           count, cursor, rows, gsig, gsh, sg, sh, t.sh_stride, o);
+    hipLaunchKernelGGL((bwd_reduce_wave_kernel<DEG, OPT>), dim3(g), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor,
+                       rows, gsig, gsh, sg, sh, t.sh_stride, o);
 }
 
-template <int DEG, bool HEAVY>
+template <int DEG>
 static void launch_wave(const dot_tree& t, const BwdArgs& a, const uint32_t* offset, const uint32_t* base0,
                         const uint32_t* count, const uint32_t* cursor, const float* rows, hipStream_t s) {
     switch (opt_kind(a)) {
-        case OPT_RMSPROP: launch_wave_opt<DEG, OPT_RMSPROP, HEAVY>(t, a, offset, base0, count, cursor, rows, s); break;
-        case OPT_ADAM: launch_wave_opt<DEG, OPT_ADAM, HEAVY>(t, a, offset, base0, count, cursor, rows, s); break;
-        default: launch_wave_opt<DEG, OPT_NONE, HEAVY>(t, a, offset, base0, count, cursor, rows, s); break;
+        case OPT_RMSPROP: launch_wave_opt<DEG, OPT_RMSPROP>(t, a, offset, base0, count, cursor, rows, s); break;
+        case OPT_ADAM: launch_wave_opt<DEG, OPT_ADAM>(t, a, offset, base0, count, cursor, rows, s); break;
+        default: launch_wave_opt<DEG, OPT_NONE>(t, a, offset, base0, count, cursor, rows, s); break;
     }
 }
+
+// workgroups of a block reduction that sum heavy buckets
+static unsigned heavy_blocks(int64_t L) { return (unsigned)std::min<int64_t>((L + RED_BLOCK - 1) / RED_BLOCK, 2048); }
 
 // buckets holding at least this many rows on average are reduced a wave per leaf
 static constexpr uint32_t kWaveRowsPerLeaf = 32;
@@ -1405,24 +1416,25 @@ static void launch_bwd_fused(const dot_tree& t, const BwdArgs& a, const uint32_t
     const FusedOpt o = fused_opt(a);
     auto a16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     const bool vec = K % 4 == 0 && t.sh_stride % 4 == 0 && a16(sh) && a16(o.v_sh) && (!a.adam || a16(o.m_sh));
-    const dim3 g(rg), b(RED_BLOCK);
+    const unsigned hb = heavy_blocks(L);
+    const dim3 g(rg + hb), b(RED_BLOCK);
     if constexpr (K % 4 == 0) {
         if (vec) {
             if (a.adam)
                 hipLaunchKernelGGL((bwd_fused_kernel<DEG, OPT_ADAM, 4>), g, b, 0, s, L, offset, base0, count, cursor,
-                                   rows, sg, sh, t.sh_stride, o);
+                                   rows, sg, sh, t.sh_stride, o, hb);
             else
                 hipLaunchKernelGGL((bwd_fused_kernel<DEG, OPT_RMSPROP, 4>), g, b, 0, s, L, offset, base0, count,
-                                   cursor, rows, sg, sh, t.sh_stride, o);
+                                   cursor, rows, sg, sh, t.sh_stride, o, hb);
             return;
         }
     }
     if (a.adam)
         hipLaunchKernelGGL((bwd_fused_kernel<DEG, OPT_ADAM, 1>), g, b, 0, s, L, offset, base0, count, cursor, rows, sg,
-                           sh, t.sh_stride, o);
+                           sh, t.sh_stride, o, hb);
     else
         hipLaunchKernelGGL((bwd_fused_kernel<DEG, OPT_RMSPROP, 1>), g, b, 0, s, L, offset, base0, count, cursor, rows,
-                           sg, sh, t.sh_stride, o);
+                           sg, sh, t.sh_stride, o, hb);
 }
 
 void note_forward(const dot_tree& t, const SegRecords& rec, const uint32_t* counts, int64_t n_rays, hipStream_t s) {
@@ -1598,13 +1610,14 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
         }
     }
     const unsigned rg = (unsigned)((L + RED_BLOCK - 1) / RED_BLOCK);
+    const unsigned hb = heavy_blocks(L);
     const bool wave_all = (uint64_t)m >= (uint64_t)kWaveRowsPerLeaf * (uint64_t)L;
     if (wave_all) {
         switch (t.degree) {
-            case 0: launch_wave<0, false>(t, a, offset, base0, count, cursor, rows, s); break;
-            case 1: launch_wave<1, false>(t, a, offset, base0, count, cursor, rows, s); break;
-            case 2: launch_wave<2, false>(t, a, offset, base0, count, cursor, rows, s); break;
-            default: launch_wave<3, false>(t, a, offset, base0, count, cursor, rows, s); break;
+            case 0: launch_wave<0>(t, a, offset, base0, count, cursor, rows, s); break;
+            case 1: launch_wave<1>(t, a, offset, base0, count, cursor, rows, s); break;
+            case 2: launch_wave<2>(t, a, offset, base0, count, cursor, rows, s); break;
+            default: launch_wave<3>(t, a, offset, base0, count, cursor, rows, s); break;
         }
     } else if (fused) {
         switch (t.degree) {
@@ -1614,17 +1627,10 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
             default: launch_bwd_fused<3>(t, a, offset, base0, count, cursor, rows, s); break;
         }
     } else switch (t.degree) {
-        case 0: hipLaunchKernelGGL(bwd_reduce_kernel<0>, dim3(rg), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh); break;
-        case 1: hipLaunchKernelGGL(bwd_reduce_kernel<1>, dim3(rg), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh); break;
-        case 2: hipLaunchKernelGGL(bwd_reduce_kernel<2>, dim3(rg), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh); break;
-        default: hipLaunchKernelGGL(bwd_reduce_kernel<3>, dim3(rg), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh); break;
-    }
-    // the heavy buckets a block reduction left out
-    if (!wave_all) switch (t.degree) {
-        case 0: launch_wave<0, true>(t, a, offset, base0, count, cursor, rows, s); break;
-        case 1: launch_wave<1, true>(t, a, offset, base0, count, cursor, rows, s); break;
-        case 2: launch_wave<2, true>(t, a, offset, base0, count, cursor, rows, s); break;
-        default: launch_wave<3, true>(t, a, offset, base0, count, cursor, rows, s); break;
+        case 0: hipLaunchKernelGGL(bwd_reduce_kernel<0>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
+        case 1: hipLaunchKernelGGL(bwd_reduce_kernel<1>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
+        case 2: hipLaunchKernelGGL(bwd_reduce_kernel<2>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
+        default: hipLaunchKernelGGL(bwd_reduce_kernel<3>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
     }
     e = hipGetLastError();
     t.scratch_put(rows, s);
