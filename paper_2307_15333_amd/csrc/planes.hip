@@ -191,6 +191,7 @@ __global__ void zero_f64_kernel(double* p) { *p = 0.0; }
 // large workgroups (a 2^20-ray batch: 256 atomics instead of 4096).
 constexpr int MSE_THREADS = 1024;
 constexpr int MSE_BLOCKS = 256;
+constexpr int MSE_RAYS = 4;
 
 __global__ __launch_bounds__(MSE_THREADS) void mse_kernel(const float* __restrict__ pred, const float* __restrict__ target,
                                                   const int64_t* __restrict__ idx, int64_t n, double gscale,
@@ -199,13 +200,36 @@ __global__ __launch_bounds__(MSE_THREADS) void mse_kernel(const float* __restric
     __shared__ double part[MSE_THREADS / WAVE];
     double acc = 0.0;
     if (gmul) gscale *= *gmul;
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = idx ? idx[r] : r;
+    // MSE_RAYS rays of a thread in flight: an id and then a target row anywhere in
+    // MSE_RAYS rays of a thread in flight: an id and then a target row anywhere in
+    // the views' images are two round trips, which bound this kernel (2^20 of 64M
+    // rays: one at a time 46.8 us, four 35.5)
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r0 < n; r0 += MSE_RAYS * stride) {
+        int64_t r[MSE_RAYS], t[MSE_RAYS];
+        float p[MSE_RAYS][3], q[MSE_RAYS][3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double e = (double)pred[3 * r + c] - (double)target[3 * t + c];   // exact
-            if (grad) grad[3 * r + c] = (float)(gscale * e);
-            acc += e * e;
+        for (int u = 0; u < MSE_RAYS; ++u) {
+            const int64_t i = r0 + u * stride;
+            r[u] = i < n ? i : r0;
+            t[u] = idx ? idx[r[u]] : r[u];
+        }
+#pragma unroll
+        for (int u = 0; u < MSE_RAYS; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                q[u][c] = target[3 * t[u] + c];
+                p[u][c] = pred[3 * r[u] + c];
+            }
+#pragma unroll
+        for (int u = 0; u < MSE_RAYS; ++u) {
+            if (r0 + u * stride >= n) break;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const double e = (double)p[u][c] - (double)q[u][c];   // exact
+                if (grad) grad[3 * r[u] + c] = (float)(gscale * e);
+                acc += e * e;
+            }
         }
     }
     if (!loss) return;
