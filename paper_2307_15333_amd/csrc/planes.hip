@@ -201,7 +201,6 @@ __global__ __launch_bounds__(MSE_THREADS) void mse_kernel(const float* __restric
     double acc = 0.0;
     if (gmul) gscale *= *gmul;
     // MSE_RAYS rays of a thread in flight: an id and then a target row anywhere in
-    // MSE_RAYS rays of a thread in flight: an id and then a target row anywhere in
     // the views' images are two round trips, which bound this kernel (2^20 of 64M
     // rays: one at a time 46.8 us, four 35.5)
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
