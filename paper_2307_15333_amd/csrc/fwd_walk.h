@@ -370,7 +370,14 @@ __device__ __forceinline__ void walk_fwd(const TreeView& tv, const Ray& r, bool 
     double t0 = 0.0, t1 = __builtin_huge_val();
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (D[a] != 0.0) {
+        if (D[a] != D[a]) {
+            // no direction (a zero vector, a broken camera): as in traverse, never
+            // left along this axis, from its first cell.  Such a ray ends in its first
+            // leaf with a NaN colour (its basis is NaN)
+            D[a] = 0.0;
+            O[a] = 0.0;
+            inv[a] = __builtin_huge_val();
+        } else if (D[a] != 0.0) {
             inv[a] = 1.0 / D[a];
             const double p = (0.0 - O[a]) * inv[a], q = (LF - O[a]) * inv[a];
             t0 = fmax(t0, fmin(p, q));
@@ -433,7 +440,7 @@ __device__ __forceinline__ void walk_fwd(const TreeView& tv, const Ray& r, bool 
             te[a] = ((double)plane[a] - O[a]) * inv[a];
         }
         const double tm = min_f64(te[0], min_f64(te[1], te[2]));
-        const bool last = !live || tm >= s1;
+        const bool last = !live || !(tm < s1);      // an origin that is not a number crosses no plane
         const double e = min_f64(max_f64(tm, s), s1);
         const float delta = (float)(e - s);
         const bool h0 = te[0] == tm, h1 = te[1] == tm, h2 = te[2] == tm;
