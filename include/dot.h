@@ -151,7 +151,9 @@ typedef struct {
  *  referenced twice or never, a child numbered before its parent (cycle or
  *  non pre-order), leaves not in DFS order, depth > DOT_MAX_DEPTH, a bad
  *  degree, storage or box; DOT_ENOMEM / DOT_EHIP from the device.
- *  The call synchronises `stream` before returning.
+ *  The call synchronises `stream` before returning; with a caller's allocator it
+ *  waits for no other stream.  The first build of a plane of 64 MiB or more allocates
+ *  32 MiB of pinned host memory, kept for later builds until the process ends.
  */
 int dot_build(const dot_tree_desc *desc, int32_t storage, const dot_allocator *alloc, void *stream,
               dot_tree_t *out);

@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -183,10 +184,17 @@ static int validate_tree(const dot_tree_desc& d, std::vector<uint8_t>& depth, in
 // slots of its own, reach the link's 57 GB/s (166 MB: 6.0 -> 3.1 ms).  A slot's
 // chunk goes straight to the plane when the rows are stored as they are, else
 // through the device stage to the encoding kernel.  Chunks are independent, so
-// their order on the stream does not matter.  False: nothing was started, the
-// caller copies by itself.
+// their order on the stream does not matter.  False: nothing was started (also
+// when another thread's upload holds the slots), the caller copies by itself.
 static constexpr size_t kSlotBytes = 4u << 20;
 static constexpr int kUploadThreads = 4, kSlotsPerThread = 2;
+
+// The pinned slots (32 MiB, allocated by the first large upload, one upload at a
+// time) stay until the process ends: releasing pinned memory waits for the whole
+// device, so a build would stall every other stream, and behind an open serving
+// queue, whose launch stays resident, it would not return before the queue ends.
+static std::mutex g_slots_mutex;
+static void* g_slots = nullptr;
 
 static bool upload_plane_threads(const Alloc& al, int storage, const float* host, void* dst, int64_t rows, int cols,
                                  int stride, hipStream_t s, hipError_t* err) {
@@ -197,17 +205,17 @@ static bool upload_plane_threads(const Alloc& al, int storage, const float* host
     const bool direct = storage == DOT_F32 && cols == stride;
     const int es = storage_bytes(storage);
     constexpr int kSlots = kUploadThreads * kSlotsPerThread;
+    std::unique_lock<std::mutex> lock(g_slots_mutex, std::try_to_lock);
+    if (!lock.owns_lock()) return false;
     int device = 0;
-    void* pinned = nullptr;
     void* stage = nullptr;
-    if (hipGetDevice(&device) != hipSuccess || hipHostMalloc(&pinned, kSlots * kSlotBytes, hipHostMallocDefault) != hipSuccess) {
+    if (hipGetDevice(&device) != hipSuccess ||
+        (!g_slots && hipHostMalloc(&g_slots, kSlots * kSlotBytes, hipHostMallocPortable) != hipSuccess)) {
         (void)hipGetLastError();
         return false;
     }
-    if (!direct && !(stage = al.get(kSlots * kSlotBytes))) {
-        (void)hipHostFree(pinned);
-        return false;
-    }
+    void* const pinned = g_slots;
+    if (!direct && !(stage = al.get(kSlots * kSlotBytes))) return false;
     hipError_t result[kUploadThreads] = {};
     auto work = [&](int t) {
         hipError_t e = hipSetDevice(device);
@@ -256,7 +264,6 @@ static bool upload_plane_threads(const Alloc& al, int storage, const float* host
     for (int t = 0; t < kUploadThreads; ++t)
         if (e == hipSuccess) e = result[t];
     if (stage) al.put(stage);
-    (void)hipHostFree(pinned);
     *err = e;
     return true;
 }
