@@ -370,14 +370,13 @@ __device__ __forceinline__ void walk_fwd(const TreeView& tv, const Ray& r, bool 
     double t0 = 0.0, t1 = __builtin_huge_val();
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        if (D[a] != D[a]) {
-            // no direction (a zero vector, a broken camera): as in traverse, never
-            // left along this axis, from its first cell.  Such a ray ends in its first
-            // leaf with a NaN colour (its basis is NaN)
-            D[a] = 0.0;
-            O[a] = 0.0;
-            inv[a] = __builtin_huge_val();
-        } else if (D[a] != 0.0) {
+        // no direction (a zero vector, a broken camera): as in traverse, never left
+        // along this axis, from its first cell.  Such a ray ends in its first leaf
+        // with a NaN colour (its basis is NaN)
+        const bool has = D[a] == D[a];
+        D[a] = has ? D[a] : 0.0;
+        O[a] = has ? O[a] : 0.0;
+        if (D[a] != 0.0) {
             inv[a] = 1.0 / D[a];
             const double p = (0.0 - O[a]) * inv[a], q = (LF - O[a]) * inv[a];
             t0 = fmax(t0, fmin(p, q));
