@@ -10,10 +10,16 @@ namespace dot {
 
 // MODE 0: plain; 1: with the traversal counters of dot_render_stats; 2: with
 // the per-leaf segment counts of a training forward; 3: the signal alone (no
-// rows are fetched, so the kernel serves every degree).  FAR: a tree with a plane
-// past the reach of 32-bit offsets, walked lane by lane with 64-bit addresses.
-template <int DT, int DEG, int MODE, bool FAR>
-__global__ __launch_bounds__(BLOCK, FAR ? 1 : MODE == 3 ? 6 : MODE == 2 ? 4 : fwd_waves(DT, DEG)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
+// rows are fetched, so the kernel serves every degree); + SUM_MODE: with a signal
+// that sums (else it keeps the maximum).  FAR: a tree with a plane past the reach
+// of 32-bit offsets, walked lane by lane with 64-bit addresses (any signal).
+constexpr int SUM_MODE = 4;
+constexpr int render_waves(int dt, int deg, int mode, bool far) {
+    return far ? 1 : mode == 3 ? 6 : mode == 2 ? 4 : fwd_waves(dt, deg);
+}
+template <int DT, int DEG, int KIND, bool FAR>
+__global__ __launch_bounds__(BLOCK, render_waves(DT, DEG, KIND % SUM_MODE, FAR)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
+    constexpr int MODE = KIND % SUM_MODE;
     __shared__ int stack_lds[LAT * BLOCK];
     __shared__ std::conditional_t<MODE == 2 && !FAR, Stage, int> stage;
     const int tid = threadIdx.x;
@@ -24,7 +30,7 @@ __global__ __launch_bounds__(BLOCK, FAR ? 1 : MODE == 3 ? 6 : MODE == 2 ? 4 : fw
     Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
     int64_t rid = 0;
     const bool live = make_ray(rb, tile, lane, r, rid);
-    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2, MODE != 3>> seg(tv, a);
+    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2, MODE != 3, KIND >= SUM_MODE>> seg(tv, a);
     seg.rid = rid;
     if constexpr (MODE == 2 && !FAR) seg.stage = &stage;
     int desc = 0;
@@ -1230,12 +1236,19 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s, uint32_t* word
     return hipGetLastError();
 }
 
+static bool sums_signal(const FwdArgs& a) { return a.signal && a.signal_mode != DOT_SIGNAL_MAX; }
+
 template <int DT, int DEG, bool FAR>
 static hipError_t fwd_dispatch_mode(const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid, hipStream_t s) {
+    constexpr int TRAIN = DT == DOT_F32 ? 2 : 0, SUM = FAR ? 0 : SUM_MODE;
     if (a.stats)
         hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 1, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else if (DT == DOT_F32 && a.leaf_count && sums_signal(a))
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, TRAIN + SUM, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
     else if (DT == DOT_F32 && a.leaf_count)
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, DT == DOT_F32 ? 2 : 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, TRAIN, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else if (sums_signal(a))
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, SUM, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
     else
         hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
     return hipGetLastError();
@@ -1257,7 +1270,10 @@ static hipError_t fwd_dispatch_reach(int deg, const TreeView& tv, const RayBatch
                                      hipStream_t s) {
     if (!tv.near) return fwd_dispatch_deg<DT, true>(deg, tv, rb, a, grid, s);
     if (!a.rgb && !a.nseg && !a.stats && !a.leaf_count) {
-        hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+        if (sums_signal(a))
+            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3 + SUM_MODE, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+        else
+            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
         return hipGetLastError();
     }
     return fwd_dispatch_deg<DT, false>(deg, tv, rb, a, grid, s);
