@@ -984,7 +984,8 @@ constexpr int RED_BLOCK = 256;
 // Degree 3, buckets over 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
 // -> 33 us with the mapping; 2^20 rays over 3.5M leaves 200 -> 188 -> 167 us.
 // The first workgroups of a block reduction do this, beside its own rather than
-// in a launch behind it: 74 + 42 -> 82 us and 650 + 180 -> 756 us.
+// in a launch behind it (74 + 42 -> 82 us and 650 + 180 -> 756 us), except for dense
+// gradients of few rows a leaf.
 template <int DEG, int OPT>
 __device__ __forceinline__ void heavy_leaves(int64_t block, int64_t n_blocks, int64_t L, const uint32_t* __restrict__ offset,
                                              const uint32_t* __restrict__ base0, const uint32_t* __restrict__ count,
@@ -1001,7 +1002,11 @@ __device__ __forceinline__ void heavy_leaves(int64_t block, int64_t n_blocks, in
     }
 }
 
-template <int DEG>
+// HEAVY: the heavy buckets are summed in the first heavy_blocks workgroups; else in a
+// launch of bwd_heavy_kernel, whose registers (108 a lane at degree 3) then do not
+// bind the light sums (80: 6 waves a SIMD instead of 4).  What is saved on one side is
+// lost on the other; kJointRowsPerLeaf is where they meet.
+template <int DEG, bool HEAVY>
 __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const uint32_t* __restrict__ offset,
                                                                const uint32_t* __restrict__ base0,
                                                                const uint32_t* __restrict__ count,
@@ -1013,12 +1018,13 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const 
     constexpr int NV = 3 * K;
     constexpr int KP = K + 1;
     __shared__ float stage[RED_BLOCK * KP];
-    if (blockIdx.x < heavy_blocks) {
-        heavy_leaves<DEG, OPT_NONE>(blockIdx.x, heavy_blocks, L, offset, base0, count, cursor, rows, gsig, gsh, nullptr,
-                                    nullptr, 0, FusedOpt{});
-        return;
-    }
-    const int64_t l0 = (int64_t)(blockIdx.x - heavy_blocks) * RED_BLOCK;
+    if constexpr (HEAVY)
+        if (blockIdx.x < heavy_blocks) {
+            heavy_leaves<DEG, OPT_NONE>(blockIdx.x, heavy_blocks, L, offset, base0, count, cursor, rows, gsig, gsh, nullptr,
+                                        nullptr, 0, FusedOpt{});
+            return;
+        }
+    const int64_t l0 = (int64_t)(blockIdx.x - (HEAVY ? heavy_blocks : 0u)) * RED_BLOCK;
     const int64_t l = l0 + threadIdx.x;
     float gs, acc[NV];
     const uint32_t m = bucket_sum_light<DEG>(l, L, offset, base0, count, cursor, rows, gs, acc);
@@ -1037,6 +1043,17 @@ __global__ __launch_bounds__(RED_BLOCK) void bwd_reduce_kernel(int64_t L, const 
             if (v != 0.f) gsh[(l0 + r) * NV + ch * K + k] += v;
         }
     }
+}
+
+template <int DEG>
+__global__ __launch_bounds__(RED_BLOCK) void bwd_heavy_kernel(int64_t L, const uint32_t* __restrict__ offset,
+                                                              const uint32_t* __restrict__ base0,
+                                                              const uint32_t* __restrict__ count,
+                                                              const uint32_t* __restrict__ cursor,
+                                                              const float* __restrict__ rows, float* __restrict__ gsig,
+                                                              float* __restrict__ gsh) {
+    heavy_leaves<DEG, OPT_NONE>(blockIdx.x, gridDim.x, L, offset, base0, count, cursor, rows, gsig, gsh, nullptr, nullptr, 0,
+                                FusedOpt{});
 }
 
 // The optimiser step on columns [ch K, ch K + K) of a block's nl leaves (rows
@@ -1220,6 +1237,29 @@ static unsigned heavy_blocks(int64_t L) { return (unsigned)std::min<int64_t>((L 
 
 // buckets holding at least this many rows on average are reduced a wave per leaf
 static constexpr uint32_t kWaveRowsPerLeaf = 32;
+
+// Dense gradients, buckets of at least this many rows on average: heavy buckets in the
+// launch of the light ones.  Whole adjoint, apart / in one launch: 0.07 rows a leaf
+// (2^14 rays, 3.5M leaves) 260 / 281 us, 0.2 (4096 rays, 2.1M) 286 / 316, 1.2 (2^18 rays,
+// 3.5M) 679 / 700, 2.6 (28.5M leaves) 9.85 / 10.6 ms; 4.7 (2^20 rays, 3.5M) 1329 / 1309 us,
+// 16 (2.1M leaves, none heavy) 1955 / 1541, 20 (100k explicit rays, 205k leaves) 311 / 272.
+static constexpr uint32_t kJointRowsPerLeaf = 4;
+
+template <int DEG>
+static void launch_reduce(const BwdArgs& a, int64_t L, uint32_t m, const uint32_t* offset, const uint32_t* base0,
+                          const uint32_t* count, const uint32_t* cursor, const float* rows, hipStream_t s) {
+    const unsigned rg = (unsigned)((L + RED_BLOCK - 1) / RED_BLOCK), hb = heavy_blocks(L);
+    const dim3 b(RED_BLOCK);
+    if ((uint64_t)m >= (uint64_t)kJointRowsPerLeaf * (uint64_t)L) {
+        hipLaunchKernelGGL((bwd_reduce_kernel<DEG, true>), dim3(rg + hb), b, 0, s, L, offset, base0, count, cursor, rows,
+                           a.grad_sigma, a.grad_sh, hb);
+        return;
+    }
+    hipLaunchKernelGGL((bwd_reduce_kernel<DEG, false>), dim3(rg), b, 0, s, L, offset, base0, count, cursor, rows,
+                       a.grad_sigma, a.grad_sh, 0u);
+    hipLaunchKernelGGL(bwd_heavy_kernel<DEG>, dim3(hb), b, 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma,
+                       a.grad_sh);
+}
 
 // p[0, n) = 0, and *word = 0 when given (one launch for an array and a counter)
 __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t* word, int n_words) {
@@ -1625,8 +1665,6 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
             default: launch_emit<DOT_BF16>(t.degree, tv, rb, ae, offset, base0, count, cursor, rows, grid, s); break;
         }
     }
-    const unsigned rg = (unsigned)((L + RED_BLOCK - 1) / RED_BLOCK);
-    const unsigned hb = heavy_blocks(L);
     const bool wave_all = (uint64_t)m >= (uint64_t)kWaveRowsPerLeaf * (uint64_t)L;
     if (wave_all) {
         switch (t.degree) {
@@ -1643,10 +1681,10 @@ hipError_t launch_render_bwd(const dot_tree& t, const RayBatch& rb, const BwdArg
             default: launch_bwd_fused<3>(t, a, offset, base0, count, cursor, rows, s); break;
         }
     } else switch (t.degree) {
-        case 0: hipLaunchKernelGGL(bwd_reduce_kernel<0>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
-        case 1: hipLaunchKernelGGL(bwd_reduce_kernel<1>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
-        case 2: hipLaunchKernelGGL(bwd_reduce_kernel<2>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
-        default: hipLaunchKernelGGL(bwd_reduce_kernel<3>, dim3(rg + hb), dim3(RED_BLOCK), 0, s, L, offset, base0, count, cursor, rows, a.grad_sigma, a.grad_sh, hb); break;
+        case 0: launch_reduce<0>(a, L, m, offset, base0, count, cursor, rows, s); break;
+        case 1: launch_reduce<1>(a, L, m, offset, base0, count, cursor, rows, s); break;
+        case 2: launch_reduce<2>(a, L, m, offset, base0, count, cursor, rows, s); break;
+        default: launch_reduce<3>(a, L, m, offset, base0, count, cursor, rows, s); break;
     }
     e = hipGetLastError();
     t.scratch_put(rows, s);
