@@ -34,12 +34,13 @@ constexpr double RAYS_PER_TILE = 16.0;
 // are neighbouring pixels and share the training forward's counting atomics
 // (one per run of lanes in a leaf).  Training forward kernel, rays in tile
 // order alone -> with cells: 2^20 rays of 3.5M leaves 1454 -> 1348 us, 2^18 rays
-// of 8.6k leaves 192 -> 162 us; the 16-fold bins cost the ordering itself about
-// 10 us more.
+// of 8.6k leaves 192 -> 162 us; the 16-fold bins cost the ordering itself 2 to 7 us.
 constexpr int32_t CELLS = 16;
 
-// fine: with cells, where tiles hold rays to order (fewer than 8 on average only
-// when even the widest tile is sparse: bins to clear and scan for nothing)
+// fine: with cells, where tiles hold rays to order.  Fewer than 8 a tile on average
+// (16 for the widest tile, whose cells of 32 pixels hold few neighbours) are not
+// worth the bins to clear and scan: 2^16 rays of 100 800x800 views, 13 a tile, order
+// 20.6 -> 30.3 us for a training forward of 241 -> 232 us.
 PixelGeo make_geo(int64_t n, int32_t W, int32_t H, int32_t n_cams, bool fine) {
     PixelGeo g;
     g.W = W;
@@ -52,7 +53,7 @@ PixelGeo make_geo(int64_t n, int32_t W, int32_t H, int32_t n_cams, bool fine) {
     g.tw = (W + (1 << shift) - 1) >> shift;
     g.tpv = (int64_t)g.tw * ((H + (1 << shift) - 1) >> shift);
     const int64_t tiles = (int64_t)n_cams * g.tpv;
-    g.cells = fine && n >= 8 * tiles ? CELLS : 1;
+    g.cells = fine && n >= (shift == 7 ? 16 : 8) * tiles ? CELLS : 1;
     g.bins = tiles * g.cells;
     return g;
 }
@@ -100,7 +101,10 @@ __global__ void k_pb_scatter(const int64_t* __restrict__ ids, int64_t n, PixelGe
 }
 
 // Few bins: every workgroup counts (and ranks) its chunk of rays in LDS, so a
-// bin takes one global atomic per workgroup instead of one per ray.
+// bin takes one global atomic per workgroup instead of one per ray.  Not with
+// cells, whose bins hold a ray or two: a workgroup's walk over them all is then
+// longer than its rays' own atomics (4000 rays of 100 64x64 views 20.1 -> 15.7 us,
+// tiles alone in LDS 17.3).
 constexpr int LDS_BINS = 4096;
 constexpr int ITEMS = 4;                // rays per thread
 constexpr int CHUNK = 256 * ITEMS;      // rays per workgroup
@@ -168,8 +172,10 @@ unsigned grid_of(int64_t n) {
 
 }  // namespace
 
+static bool few_bins(const PixelGeo& g) { return g.cells == 1 && g.bins <= LDS_BINS; }
+
 static size_t geo_bytes(const PixelGeo& g, int64_t n) {
-    const int64_t ranks = g.bins <= LDS_BINS ? 0 : n;    // the many-bin path keeps each ray's rank
+    const int64_t ranks = few_bins(g) ? 0 : n;    // the many-bin path keeps each ray's rank
     return sizeof(uint32_t) * (size_t)(2 * g.bins + scan_scratch_elems(g.bins) + 1 + ranks);
 }
 
@@ -193,7 +199,7 @@ hipError_t launch_pixel_batch(const int64_t* ids, int64_t n, int32_t W, int32_t 
     uint32_t* bsum = cursor + g.bins;
     uint32_t* tot = bsum + scan_scratch_elems(g.bins);
     uint32_t* rank = tot + 1;
-    const bool lds = g.bins <= LDS_BINS;
+    const bool lds = few_bins(g);
     const unsigned gl = (unsigned)((n + CHUNK - 1) / CHUNK);
     hipLaunchKernelGGL(k_pb_zero, dim3(grid_of(g.bins)), dim3(256), 0, s, count, g.bins);
     if (lds)
