@@ -420,8 +420,10 @@ int dot_sigma_signal(dot_tree_t tree, float *signal_out, void *stream);
  *  Writes the same rays as a DOT_RAYS_PIXELS list, cam_idx_out / pix_idx_out
  *  (DEVICE int32 [n]), grouped by screen tile -- square tiles sized to hold
  *  about 16 of the batch's rays, in camera-then-row-major tile order; order
- *  inside a tile unspecified (with a workspace of the size asked for below,
- *  near pixels are kept together) -- so that a wave traces neighbouring pixels.
+ *  inside a tile unspecified -- so that a wave traces neighbouring pixels.  (With a
+ *  workspace of the size asked for below, tiles of enough rays are ordered by their
+ *  4 x 4 cells too, as long as that takes no more than DOT_PIXEL_BATCH_SCRATCH_BYTES:
+ *  up to about 2.2M rays of 100 views at 800x800.  A larger workspace changes nothing.)
  *  ray_ids_out (DEVICE int64 [n] or NULL) receives the ids in the new order,
  *  for use as the target rows of dot_mse_loss.  The batch's content is
  *  unchanged (the loss is a mean and the gradient a sum over it).

@@ -7,6 +7,7 @@
 // the gradient a sum over the batch).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "dot_internal.h"
@@ -179,8 +180,9 @@ static size_t geo_bytes(const PixelGeo& g, int64_t n) {
     return sizeof(uint32_t) * (size_t)(2 * g.bins + scan_scratch_elems(g.bins) + 1 + ranks);
 }
 
-// What a call needs at least (tiles alone), and what it takes to order the
-// cells too, unless that passes the size of the no-allocation scratch.
+// What a call needs at least (tiles alone), and what it takes to order the cells
+// too, unless that passes the size of the no-allocation scratch (callers may ask
+// dot_pixel_batch_workspace whether a batch fits there).
 size_t pixel_batch_workspace_min(int64_t n, int32_t W, int32_t H, int32_t n_cams) {
     return geo_bytes(make_geo(n, W, H, n_cams, false), n);
 }
@@ -192,8 +194,10 @@ size_t pixel_batch_workspace_bytes(int64_t n, int32_t W, int32_t H, int32_t n_ca
 hipError_t launch_pixel_batch(const int64_t* ids, int64_t n, int32_t W, int32_t H, int32_t n_cams, int32_t* cam_out,
                               int32_t* pix_out, int64_t* id_out, void* ws, size_t ws_bytes, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    // the order that the workspace of pixel_batch_workspace_bytes is for: a larger one,
+    // kept from another call, does not change it
     PixelGeo g = make_geo(n, W, H, n_cams, true);
-    if (geo_bytes(g, n) > ws_bytes) g = make_geo(n, W, H, n_cams, false);
+    if (geo_bytes(g, n) > std::min(ws_bytes, pixel_batch_workspace_bytes(n, W, H, n_cams))) g = make_geo(n, W, H, n_cams, false);
     uint32_t* count = static_cast<uint32_t*>(ws);
     uint32_t* cursor = count + g.bins;
     uint32_t* bsum = cursor + g.bins;
