@@ -441,6 +441,16 @@ struct Temps {
         ps.push_back(p);
         return static_cast<T*>(p);
     }
+    // give one back early
+    template <class T>
+    void put(T*& p) {
+        for (void*& q : ps)
+            if (q == p) {
+                al.put(q);
+                q = nullptr;
+            }
+        p = nullptr;
+    }
     ~Temps() {
         for (void* p : ps) al.put(p);
     }
@@ -560,7 +570,13 @@ int refine_tree(dot_tree& t, const float* signal, const dot_refine_params& p, do
     if (e != hipSuccess) return hip_fail(e, "dot_refine: sizes");
     const int64_t L2 = (int64_t)h_tot[0], I2 = (int64_t)h_tot[1];
 
-    // 4. new planes
+    // 4. new planes; what only the counts needed goes back first, which makes room
+    // for the list of sources (4 B per new leaf; 24 B per old leaf go back)
+    tmp.put(keys);
+    tmp.put(unsel);
+    tmp.put(pre_unsel);
+    tmp.put(cnt);
+    tmp.put(hist_first);
     int32_t* child2 = static_cast<int32_t*>(t.alloc.get((size_t)std::max<int64_t>(I2, 1) * 32));
     void* sig2 = t.alloc.get((size_t)L2 * es);
     void* sh2 = t.alloc.get((size_t)L2 * stride * es);
