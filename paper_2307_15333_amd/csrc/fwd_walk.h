@@ -36,8 +36,15 @@ __device__ __forceinline__ Rsrc plane_rsrc(const void* p, uint64_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(uint32_t)bytes, 0x00020000);
 }
 
-// waves per SIMD that the forward kernels are held to
-constexpr int fwd_waves(int dt, int deg) { return dt == DOT_F32 && deg >= 2 ? 4 : 5; }
+// waves per SIMD that the forward kernels are held to: as many as their registers
+// allow without spills in the walk.  8 views of 800x800, us at 4 / 5 / 6 waves: FP32 of
+// degree 3 1240 / 2500 / -, of degree 2 580 / 595 / -, FP16 965 / 945 / 1367, BF16
+// 975 / 1012 / 1564, palette 901 / 897 / 1290 (degree 3 all); the rest is within 2 % at
+// 3 to 6.
+constexpr int fwd_waves(int dt, int deg) {
+    if (deg <= 1) return 6;
+    return dt == DOT_F32 || (dt == DOT_BF16 && deg == 3) ? 4 : 5;
+}
 
 template <int CTRL>
 __device__ __forceinline__ int quad_i(int v) {

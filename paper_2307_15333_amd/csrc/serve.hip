@@ -60,12 +60,11 @@ constexpr int CTR_STRIDE = 16;   // 64-bit counters per 128-byte line
 constexpr int JOB_KINDS = 4;     // storage types
 
 // LINKED: every tree of the batch is near and has links (the usual case); the
-// kernel then holds one walk instead of three and the waves of render_fwd (96
-// VGPRs instead of 123 for FP16).  A burst of 24 requests over four FP16 trees:
-// 4.16 ms with the lane-by-lane walk and the claim before each tile, 3.98 with
-// the three walks, 3.26 with the one and the claim ahead.
+// kernel then holds one walk instead of three.  Four waves a SIMD: with every degree in
+// one kernel five spill, and a burst of 24 requests over FP16 trees, 0.7 ms of it the
+// admission on the host, takes 3.67 ms instead of 3.49.
 template <int DT, bool LINKED>
-__global__ __launch_bounds__(BLOCK, LINKED ? fwd_waves(DT, 3) : 4) void render_jobs_kernel(const JobDev* __restrict__ jobs,
+__global__ __launch_bounds__(BLOCK, 4) void render_jobs_kernel(const JobDev* __restrict__ jobs,
                                                             const int64_t* __restrict__ prefix, int n_jobs,
                                                             unsigned long long* __restrict__ counters) {
     __shared__ int stack_lds[LAT * BLOCK];
