@@ -75,9 +75,12 @@ struct Stage {
 
 // The ray's compositing state (see FwdSeg, which computes the same per lane).
 // COLOUR = false: the weights alone (the signal pass), which need no row: 16
-// views of 800x800 over 3.5M FP32 leaves 3.11 -> 1.43 ms.  SUM: the signal sums
-// (its own instantiations: the registers it takes cost the other modes 3 to 6 %).
-template <int DT, int DEG, bool COUNT = false, bool COLOUR = true, bool SUM = false>
+// views of 800x800 over 3.5M FP32 leaves 3.11 -> 1.43 ms.  SIGNAL: none, the largest
+// weight of a leaf or the sum of its weights; in instantiations of their own, since the
+// registers of the sums cost the other forms 3 to 6 %, and those of the maximum a 64x64
+// view of FP16 leaves 55 us instead of 50.
+enum { SIGNAL_NONE = 0, SIGNAL_MAX = 1, SIGNAL_SUM = 2 };
+template <int DT, int DEG, bool COUNT = false, bool COLOUR = true, int SIGNAL = SIGNAL_NONE>
 struct FwdWave {
     static constexpr int K = (DEG + 1) * (DEG + 1);
     static constexpr bool QUAD = DT == DOT_F32 && DEG == 3;
@@ -249,8 +252,7 @@ struct FwdWave {
 
     // the stored signal, read for the max filter, in = false: nothing
     __device__ __forceinline__ void fetch_signal(int leaf, bool in, Fetch& f) {
-        f.cur = 0.f;
-        if (!SUM && a.signal) {
+        if constexpr (SIGNAL == SIGNAL_MAX) {
             const Rsrc rs = plane_rsrc(a.signal, (uint64_t)tv.n_leaves * 4);
             f.cur = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, in ? (uint32_t)leaf * 4u : OFF_NONE, 0, 0));
         }
@@ -346,9 +348,8 @@ struct FwdWave {
                     C[ch] = fmaf(w, cv[ch], C[ch]);
                 }
             }
-            if constexpr (SUM)
-                ws = w;
-            else if (a.signal) {
+            if constexpr (SIGNAL == SIGNAL_SUM) ws = w;
+            if constexpr (SIGNAL == SIGNAL_MAX) {
                 // non-negative floats order like their bit patterns; skip the
                 // atomic when the stored value already dominates
                 if (w > f.cur) atomicMax(reinterpret_cast<unsigned int*>(&a.signal[leaf]), __float_as_uint(w));
@@ -356,7 +357,7 @@ struct FwdWave {
             S = Sn;
             T = Tn;
         }
-        if constexpr (SUM) add_signal(leaf, ws, in);
+        if constexpr (SIGNAL == SIGNAL_SUM) add_signal(leaf, ws, in);
         if constexpr (COUNT) {
             const bool counted = in && sg > 0.f;
             if (__any(counted)) {

@@ -10,19 +10,17 @@ namespace dot {
 
 // MODE 0: plain; 1: with the traversal counters of dot_render_stats; 2: with
 // the per-leaf segment counts of a training forward; 3: the signal alone (no
-// rows are fetched, so the kernel serves every degree); + SUM_MODE: with a signal
-// that sums (else it keeps the maximum).  FAR: a tree with a plane past the reach
-// of 32-bit offsets, walked lane by lane with 64-bit addresses (any signal).
-constexpr int SUM_MODE = 4;
+// rows are fetched, so the kernel serves every degree).  FAR: a tree with a plane
+// past the reach of 32-bit offsets, walked lane by lane with 64-bit addresses (which
+// looks at the signal's kind as it runs: SIGNAL is not used).
 // The signal alone is within 1 % at 5 and 6 waves a SIMD and 3 % slower at 8.  A
 // training forward of degree 3 spills at 4, in the walk and in flush (2^20 rays of 3.5M
 // leaves 1350 us, 1285 at 3); below degree 3 it is within 2 % either way.
 constexpr int render_waves(int dt, int deg, int mode, bool far) {
     return far ? 1 : mode == 3 ? 6 : mode == 2 ? (deg == 3 ? 3 : 4) : fwd_waves(dt, deg);
 }
-template <int DT, int DEG, int KIND, bool FAR>
-__global__ __launch_bounds__(BLOCK, render_waves(DT, DEG, KIND % SUM_MODE, FAR)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
-    constexpr int MODE = KIND % SUM_MODE;
+template <int DT, int DEG, int MODE, int SIGNAL, bool FAR>
+__global__ __launch_bounds__(BLOCK, render_waves(DT, DEG, MODE, FAR)) void render_fwd_kernel(TreeView tv, RayBatch rb, FwdArgs a) {
     __shared__ int stack_lds[LAT * BLOCK];
     __shared__ std::conditional_t<MODE == 2 && !FAR, Stage, int> stage;
     const int tid = threadIdx.x;
@@ -33,7 +31,7 @@ __global__ __launch_bounds__(BLOCK, render_waves(DT, DEG, KIND % SUM_MODE, FAR))
     Ray r{0.0, 0.0, 0.0, 1.0, 0.0, 0.0};
     int64_t rid = 0;
     const bool live = make_ray(rb, tile, lane, r, rid);
-    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2, MODE != 3, KIND >= SUM_MODE>> seg(tv, a);
+    std::conditional_t<FAR, FwdSeg<DT, DEG, MODE == 2>, FwdWave<DT, DEG, MODE == 2, MODE != 3, SIGNAL>> seg(tv, a);
     seg.rid = rid;
     if constexpr (MODE == 2 && !FAR) seg.stage = &stage;
     int desc = 0;
@@ -1279,32 +1277,34 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t n, hipStream_t s, uint32_t* word
     return hipGetLastError();
 }
 
-static bool sums_signal(const FwdArgs& a) { return a.signal && a.signal_mode != DOT_SIGNAL_MAX; }
+template <int DT, int DEG, int SIGNAL, bool FAR>
+static hipError_t fwd_dispatch_mode(const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid, hipStream_t s) {
+    if (SIGNAL == SIGNAL_NONE && a.stats)      // dot_render_stats asks for no signal
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 1, SIGNAL_NONE, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else if (DT == DOT_F32 && a.leaf_count)
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, DT == DOT_F32 ? 2 : 0, SIGNAL, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    else
+        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0, SIGNAL, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    return hipGetLastError();
+}
 
 template <int DT, int DEG, bool FAR>
-static hipError_t fwd_dispatch_mode(const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid, hipStream_t s) {
-    constexpr int TRAIN = DT == DOT_F32 ? 2 : 0, SUM = FAR ? 0 : SUM_MODE;
-    if (a.stats)
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 1, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    else if (DT == DOT_F32 && a.leaf_count && sums_signal(a))
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, TRAIN + SUM, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    else if (DT == DOT_F32 && a.leaf_count)
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, TRAIN, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    else if (sums_signal(a))
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, SUM, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    else
-        hipLaunchKernelGGL((render_fwd_kernel<DT, DEG, 0, FAR>), grid, dim3(BLOCK), 0, s, tv, rb, a);
-    return hipGetLastError();
+static hipError_t fwd_dispatch_signal(const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid, hipStream_t s) {
+    if constexpr (!FAR) {
+        if (a.signal && a.signal_mode == DOT_SIGNAL_MAX) return fwd_dispatch_mode<DT, DEG, SIGNAL_MAX, FAR>(tv, rb, a, grid, s);
+        if (a.signal) return fwd_dispatch_mode<DT, DEG, SIGNAL_SUM, FAR>(tv, rb, a, grid, s);
+    }
+    return fwd_dispatch_mode<DT, DEG, SIGNAL_NONE, FAR>(tv, rb, a, grid, s);
 }
 
 template <int DT, bool FAR>
 static hipError_t fwd_dispatch_deg(int deg, const TreeView& tv, const RayBatch& rb, const FwdArgs& a,
                                    dim3 grid, hipStream_t s) {
     switch (deg) {
-        case 0: return fwd_dispatch_mode<DT, 0, FAR>(tv, rb, a, grid, s);
-        case 1: return fwd_dispatch_mode<DT, 1, FAR>(tv, rb, a, grid, s);
-        case 2: return fwd_dispatch_mode<DT, 2, FAR>(tv, rb, a, grid, s);
-        default: return fwd_dispatch_mode<DT, 3, FAR>(tv, rb, a, grid, s);
+        case 0: return fwd_dispatch_signal<DT, 0, FAR>(tv, rb, a, grid, s);
+        case 1: return fwd_dispatch_signal<DT, 1, FAR>(tv, rb, a, grid, s);
+        case 2: return fwd_dispatch_signal<DT, 2, FAR>(tv, rb, a, grid, s);
+        default: return fwd_dispatch_signal<DT, 3, FAR>(tv, rb, a, grid, s);
     }
 }
 
@@ -1312,11 +1312,11 @@ template <int DT>
 static hipError_t fwd_dispatch_reach(int deg, const TreeView& tv, const RayBatch& rb, const FwdArgs& a, dim3 grid,
                                      hipStream_t s) {
     if (!tv.near) return fwd_dispatch_deg<DT, true>(deg, tv, rb, a, grid, s);
-    if (!a.rgb && !a.nseg && !a.stats && !a.leaf_count) {
-        if (sums_signal(a))
-            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3 + SUM_MODE, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+    if (a.signal && !a.rgb && !a.nseg && !a.stats && !a.leaf_count) {
+        if (a.signal_mode == DOT_SIGNAL_MAX)
+            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, SIGNAL_MAX, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
         else
-            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
+            hipLaunchKernelGGL((render_fwd_kernel<DT, 0, 3, SIGNAL_SUM, false>), grid, dim3(BLOCK), 0, s, tv, rb, a);
         return hipGetLastError();
     }
     return fwd_dispatch_deg<DT, false>(deg, tv, rb, a, grid, s);
