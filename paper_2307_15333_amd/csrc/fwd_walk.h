@@ -19,7 +19,7 @@
 // Measured against the lane-by-lane walk (traverse), same images, one MI355X:
 // 8 random 800x800 views of 3.5M FP32 leaves of degree 3 1.68 -> 1.30 ms (cache
 // lookups per launch 7.6e8 -> 4.3e8), a 64x64 view of 8.6k leaves 47 -> 26 us, a
-// 333x217 view of 0.87M BF16 leaves 113 -> 70 us, a 1920x1080 view of 3.5M FP16
+// 333x217 view of 0.87M BF16 leaves 113 -> 68 us, a 1920x1080 view of 3.5M FP16
 // leaves 648 -> 526 us.
 #pragma once
 
@@ -195,7 +195,8 @@ struct FwdWave {
     // bucket.  A ray's records lie in groups of four, so writing several steps
     // together fills a group's lines while the L2 still holds them, and the atomics
     // of those steps are in flight together (forward of 2^20 cell-ordered rays of
-    // 3.5M leaves: 1468 us when every step writes and counts by itself, 1348 so).
+    // 3.5M leaves, four waves a SIMD: 1468 us when every step writes and counts by
+    // itself, 1348 so).
     // Called by all lanes of the wave.
     __device__ __forceinline__ void flush() {
         if constexpr (COUNT) {

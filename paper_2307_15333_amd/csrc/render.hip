@@ -559,12 +559,15 @@ __device__ __forceinline__ void replay_rays(const RayBatch& rb, const BwdArgs& a
     }
     const float d[3] = {(float)r.dx, (float)r.dy, (float)r.dz};
     float S = 0.f, T = 1.f, P[3] = {0.f, 0.f, 0.f};
-    // four records at a time (a group of the layout), the next group and this
-    // one's bucket offsets requested before this one's rows are written.  A slot
-    // is below its leaf's recorded count by construction; records of another
+    // four records at a time (a group of the layout), their bucket offsets together.
+    // A slot is below its leaf's recorded count by construction; records of another
     // batch or tree are caught only as far as staying in bounds goes (leaf id < L,
     // row < n_rows), so the one per-leaf read is the offset.  (One record at a
-    // time: 716 us for the 16.6M records of 2^20 rays over 3.5M leaves, 586 so.)
+    // time: 723 us for the 16.7M records of 2^20 rays over 3.5M leaves, 603 so.)  The
+    // next group is read before this one's rows are written, but the compiler waits
+    // for it there, in front of the rows: the two ways to load meet in memory (q.s).
+    // With q.s as a vector it stays in flight, which the scattered rows, the bound
+    // here, do not reward: 618 us; 2^18 rays 45.0 -> 44.8, 4096 rays 19.0 -> 18.1.
     struct Group {
         float4 A[4];
         float2 B[4];
@@ -656,7 +659,10 @@ __global__ __launch_bounds__(BLOCK) void bwd_emit_rec_kernel(RayBatch rb, BwdArg
 // forward), one ray per lane: the recorded first `cap` contributing segments only
 // advance the prefix sums, the rest are emitted.  These rays are few and long, a
 // launch of their own left most of the chip idle while they walked (100k explicit
-// rays, degree 3: 139 + 116 us in two launches, 180 us in one).
+// rays, degree 3: 139 + 116 us in two launches, 180 us in one).  It pays for any number
+// of them, though the walk's registers then bind the replay too (3 waves a SIMD instead
+// of 5): whole adjoints of 2^20, 2^18 and 2^14 rays over 3.5M leaves with 130, 37 and 5
+// such rays 1376, 859 and 604 us, in two launches 1609, 942 and 653.
 template <int DEG, bool FAR>
 __global__ __launch_bounds__(BLOCK) void bwd_emit_rest_kernel(TreeView tv, RayBatch rb, BwdArgs a, int64_t nlist,
                                                               unsigned list_blocks, const uint32_t* offset,
@@ -982,7 +988,7 @@ constexpr int RED_BLOCK = 256;
 // heavy leaves (neighbours in space collect rows together) spreads over
 // neighbouring waves instead of queueing in one.  Neighbouring waves sit on one
 // XCD, so that a line of the counts is read into one L2 and not into four.
-// Degree 3, buckets over 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
+// Degree 3, with a limit of 64 rows: 100k explicit rays 76 -> 42 us with wave_fold
 // -> 33 us with the mapping; 2^20 rays over 3.5M leaves 200 -> 188 -> 167 us.
 // The first workgroups of a block reduction do this, beside its own rather than
 // in a launch behind it (74 + 42 -> 82 us and 650 + 180 -> 756 us), except for dense
