@@ -328,14 +328,19 @@ __device__ __forceinline__ void serve_tile(const ServeJob& j, int64_t t, int lan
         __hip_atomic_store(o + c, rgb[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Three waves a SIMD (at most 168 of its 512 VGPRs each), so that the queue's waves
-// leave registers on every SIMD whichever way its workgroups are packed: with four
-// waves of 128 a SIMD was full, and no kernel of any other stream started before the
-// queue closed, even with two workgroups per CU fewer.  24 requests at once over
-// three FP16 trees: 1.76 ms with three waves, 1.77 with four.
+// Three waves a SIMD, so that the queue's waves leave registers on every SIMD
+// whichever way its workgroups are packed: with four waves of 128 VGPRs a SIMD was
+// full, and no kernel of any other stream started before the queue closed, even with
+// two workgroups per CU fewer.  A kernel must not need fewer than 136 VGPRs for that
+// (three of them leave 104 of 512; FP32 needs 152).  The statement at its start takes
+// them; the compiler's own bound on the waves pads with an accumulation register
+// instead, beside which kernels of about 128 VGPRs (a render of degree 3) did not
+// start.  24 requests at once over three FP16 trees: 1.76 ms with three waves, 1.77
+// with four.
 template <int DT>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) void serve_loop_kernel(ServeHostCtl* ctl, const ServeJob* hjobs, uint64_t* hdone,
-                                                           ServeDevice dv, int max_jobs, uint64_t limit_ticks) {
+__global__ __launch_bounds__(BLOCK, 3) void serve_loop_kernel(ServeHostCtl* ctl, const ServeJob* hjobs, uint64_t* hdone,
+                                                              ServeDevice dv, int max_jobs, uint64_t limit_ticks) {
+    asm volatile("" ::: "v135");
     __shared__ int stack_lds[LAT * BLOCK];   // the walk's ancestor stacks; the feeder's chunk cursors
     static_assert(LAT * BLOCK >= WAVE * kRings, "feeder cursors fit in the stack array");
     const int tid = threadIdx.x;

@@ -21,12 +21,12 @@ def small_tree(storage, degree=3):
     return tree
 
 
-def streams_that_run(streams, buffers, seconds):
-    """Those of the streams whose kernel completes in time (one that shares a hardware queue with the launch waits)."""
+def streams_that_run(streams, work, seconds):
+    """Those of the streams whose work completes in time (one that shares a hardware queue with the launch waits)."""
     events = []
-    for s, b in zip(streams, buffers):
+    for s, f in zip(streams, work):
         with torch.cuda.stream(s):
-            b.add_(1.0)
+            f()
             events.append(s.record_event())
     end = time.perf_counter() + seconds
     while time.perf_counter() < end and not all(e.query() for e in events):
@@ -35,20 +35,26 @@ def streams_that_run(streams, buffers, seconds):
 
 
 @pytest.mark.parametrize("storage", ["f32", "f16", "bf16", "pal16"])
-def test_other_kernels_run_beside_an_open_queue(storage):
+@pytest.mark.parametrize("work", ["fill", "render", "train"])
+def test_other_kernels_run_beside_an_open_queue(storage, work):
+    """A small kernel, and the library's own of about 128 and 144 registers a lane."""
     tree = small_tree(storage)
     want = tree.render(core.Rays.cameras(np.asarray(CAM).reshape(1))).reshape(48, 64, 3)
     outs = [torch.zeros((48, 64, 3), device="cuda") for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(5)]
     buffers = [torch.zeros(1 << 20, device="cuda") for _ in streams]
-    for s, b in zip(streams, buffers):
+    other = small_tree("f32")
+    rays = core.Rays.cameras(synth.random_sphere_cameras(2, 4.0, 100, 80, 1))
+    fs = {"fill": [lambda b=b: b.add_(1.0) for b in buffers], "render": [lambda: other.render(rays)] * 5,
+          "train": [lambda: other.render_train(rays)] * 5}[work]
+    for s, f in zip(streams, fs):
         with torch.cuda.stream(s):
-            b.add_(1.0)
+            f()
     torch.cuda.synchronize()
     q = serve.Queue(storage, max_jobs=8, max_seconds=3.0)
     try:
         q.wait(q.push(tree, CAM, outs[0], 64, 48))
-        ran = streams_that_run(streams, buffers, 0.3)
+        ran = streams_that_run(streams, fs, 0.3)
         q.wait(q.push(tree, CAM, outs[1], 64, 48))      # it is still open
     finally:
         q.close()
@@ -72,7 +78,7 @@ def test_build_beside_an_open_queue():
     q = serve.Queue("f16", max_jobs=8, max_seconds=6.0)
     try:
         q.wait(q.push(tree, CAM, out, 64, 48))
-        ran = streams_that_run(streams, buffers, 0.3)
+        ran = streams_that_run(streams, [lambda b=b: b.add_(1.0) for b in buffers], 0.3)
         assert ran
         with torch.cuda.stream(ran[0]):
             built = core.Octree(large.child, sigma, sh, 1)
